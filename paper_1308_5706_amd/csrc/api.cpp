@@ -31,10 +31,23 @@ struct DevBuf {
 // copy throughout, so a call in flight on another stream keeps a consistent shape (tile
 // lists are kept until the plan is freed).
 struct Shape {
-    int R = 0, group = 0, nblk = 0;
-    const int2 *tiles_fwd = nullptr, *tiles_adj = nullptr;
-    int nfwd_plain = 0, nfwd_x = 0, nadj_plain = 0, nadj_x = 0;
-    size_t s_F = 0;                             // per-map partial-sum elements
+    // analysis tiles: those of R slots, or by the waves of the call (wig_slots) one of several
+    // numbers of slots (the results do not depend on it)
+    struct Fwd {
+        int R = 0;
+        const int4 *tiles = nullptr;
+        int nplain = 0, nx = 0;
+    } fwd[3];
+    int nfwd = 0;
+    // synthesis tiles: R slots, the m' per partial sum, their number and per-map elements; [0] FP64,
+    // [1] mixed precision (whose FP32 sums are rounded by group)
+    struct Adj {
+        int R = 0, group = 0, nblk = 0;
+        const int4 *tiles = nullptr;
+        int nplain = 0, nx = 0;
+        size_t s_F = 0;
+    } adj[2];
+    size_t s_F() const { return std::max(adj[0].s_F, adj[1].s_F); }
     int chunk = 1;                              // maps per batched launch sequence (tunable)
     // the fused alpha and gamma kernels of the prime-factor lengths (tunable): 0 never,
     // 1 where they were measured faster than the two-pass form (fuse_fwd, fuse_adj),
@@ -49,6 +62,7 @@ struct Plan {
     SegTab seg{};
     ScaleTab sc{};
     int eoff = 0;
+    int kstride = 0, ustride = 0;               // rows of the kappa sigma Delta and u tables
     // sample grid of each scale: full resolution (band-limit L for every scale) or
     // multiresolution (the scale's own band-limit Lj); W of a map holds the scales back to back
     int grid = S2DW_GRID_MW;
@@ -89,6 +103,9 @@ struct Plan {
     std::map<int, GridTab> gt;
     // device tables
     double *pq = nullptr, *uv = nullptr;        // rescaled recurrence factors pt_l(m), ut_l(m')
+    WigSeg *segs = nullptr;
+    int *rowl = nullptr;                        // l of each table row (8 per table block), -1: outside its segment
+    int rows = 0;
     double *gsc = nullptr;                      // [L][Lp] g_l(m): D = Delta / (g_l(m) h_l(m'))
     double2 *tgf = nullptr, *tga = nullptr;     // gamma pass factors [2N-1][Nh]
     double *kb2 = nullptr, *seed = nullptr, *seedm = nullptr, *phi = nullptr, *fac = nullptr;
@@ -96,7 +113,7 @@ struct Plan {
     Shape cur;                                  // current tile shape (guarded by g_mu)
     // tile lists per number R of m' slots per wave (the Wigner tile shape), built on demand
     struct TileSet {
-        int2 *fwd = nullptr, *adj = nullptr;
+        int4 *fwd = nullptr, *adj = nullptr;
         int nfwd_plain = 0, nfwd_x = 0, nadj_plain = 0, nadj_x = 0;
     };
     std::map<int, TileSet> tilesets;
@@ -128,7 +145,7 @@ struct Plan {
 };
 
 // Workspace of one stream: room for `cap` maps of a batch, map i at i * Plan::s_* (the
-// partial sums at i * Shape::s_F, room for cap * s_F elements).
+// partial sums at i * Shape::Adj::s_F, room for cap * s_F elements).
 struct Work {
     int cap = 0;
     size_t s_F = 0;
@@ -340,11 +357,24 @@ void build_tiles(const Plan &pl, const std::vector<int> &seede, int Lp, int mgro
     xn = xcd_order(b, (int)(a.size() % 8), mmajor);
 }
 
+// The tiles of both lists with the segment and the table block their l-range starts in.
+std::vector<int4> with_starts(const Plan &P, const std::vector<int2> &plain, const std::vector<int2> &xn) {
+    std::vector<int4> out;
+    for (const std::vector<int2> *v : {&plain, &xn})
+        for (const int2 &t : *v) {
+            const int l = std::max(t.x, t.y);
+            int si = 0;
+            while (P.seg.s1[si] <= l) ++si;
+            out.push_back(make_int4(t.x, t.y, si, P.seg.b0[si] + l / 8 - P.seg.s0[si] / 8));
+        }
+    return out;
+}
+
 // Selects the Wigner tile shape: R m' slots per wave (the analysis workgroup covers 4R
 // m', the synthesis one kAdjWaves R).  Tile lists are built once per R and kept.  Caller
 // holds g_mu.  Calls in flight keep the shape they copied; a stream whose workspace is too
 // small for the new partial-sum layout gets a larger one at its next call.
-int set_slots(Plan &P, int R) {
+int tile_set(Plan &P, int R, const Plan::TileSet *&out) {
     auto it = P.tilesets.find(R);
     if (it == P.tilesets.end()) {
         Plan::TileSet ts;
@@ -358,23 +388,35 @@ int set_slots(Plan &P, int R) {
         ts.nfwd_x = (int)x_a.size();
         ts.nadj_plain = (int)pl_s.size();
         ts.nadj_x = (int)x_s.size();
-        pl_a.insert(pl_a.end(), x_a.begin(), x_a.end());
-        pl_s.insert(pl_s.end(), x_s.begin(), x_s.end());
-        if (!upload(P, ts.fwd, pl_a) || !upload(P, ts.adj, pl_s)) return S2DW_E_NOMEM;
+        if (!upload(P, ts.fwd, with_starts(P, pl_a, x_a)) || !upload(P, ts.adj, with_starts(P, pl_s, x_s)))
+            return S2DW_E_NOMEM;
         it = P.tilesets.emplace(R, ts).first;
     }
-    const Plan::TileSet &ts = it->second;
-    Shape &sh = P.cur;
-    sh.R = R;
-    sh.tiles_fwd = ts.fwd;
-    sh.tiles_adj = ts.adj;
-    sh.nfwd_plain = ts.nfwd_plain;
-    sh.nfwd_x = ts.nfwd_x;
-    sh.nadj_plain = ts.nadj_plain;
-    sh.nadj_x = ts.nadj_x;
-    sh.group = kAdjWaves * R;
-    sh.nblk = (P.L + sh.group - 1) / sh.group;
-    sh.s_F = (size_t)sh.nblk * P.L * P.Lp;
+    out = &it->second;
+    return S2DW_OK;
+}
+
+// Sets the plan's shape to R slots in the analysis and in both precisions of the synthesis;
+// by_size (the default shape): by the size of the call, and of one map in the synthesis.
+int set_slots(Plan &P, int R, bool by_size = false) {
+    const Plan::TileSet *ts = nullptr;
+    Shape sh = P.cur;
+    sh.nfwd = 0;
+    int Ropt[3] = {R};
+    const int nopt = by_size ? wig_slot_options(P.K, Ropt) : 1;
+    for (int i = 0; i < nopt; ++i) {
+        int rc = tile_set(P, Ropt[i], ts);
+        if (rc != S2DW_OK) return rc;
+        sh.fwd[sh.nfwd++] = {Ropt[i], ts->fwd, ts->nfwd_plain, ts->nfwd_x};
+    }
+    for (int f32 = 0; f32 < 2; ++f32) {
+        const int Ra = by_size ? wig_adj_slots(P.K, (long)(P.Lp / 64) * P.L, f32) : R;
+        int rc = tile_set(P, Ra, ts);
+        if (rc != S2DW_OK) return rc;
+        const int group = kAdjWaves * Ra, nblk = (P.L + group - 1) / group;
+        sh.adj[f32] = {Ra, group, nblk, ts->adj, ts->nadj_plain, ts->nadj_x, (size_t)nblk * P.L * P.Lp};
+    }
+    P.cur = sh;
     return S2DW_OK;
 }
 
@@ -386,7 +428,7 @@ Shape shape_of(Plan &P) {
 
 // Default maps per batched launch sequence: as many as fit 8 GiB of workspace, at most 64.
 int default_chunk(const Plan &P) {
-    const double per_map = 16.0 * (double)(P.s_fpad + P.s_U + P.s_Ub + P.s_Y + P.cur.s_F);
+    const double per_map = 16.0 * (double)(P.s_fpad + P.s_U + P.s_Ub + P.s_Y + P.cur.s_F());
     return (int)std::max(1.0, std::min(64.0, std::floor(8.0 * (1ull << 30) / per_map)));
 }
 
@@ -562,23 +604,76 @@ int build_plan(int kind, int L, int N, double lam, int J_min, int grid, Plan *&o
     std::vector<double> ncol;
     build_delta_ncols(dt, t.nk, ncol);
     const int K = t.K, Lp = dt.Lp;
-    // one record of padding at the end: the analysis kernel reads the entries of step l + 1
-    // ahead of step l, also after the last step of the last row
-    std::vector<double> kb2((size_t)Lp * L * 2 * K + 2 * K, 0.0);
+    // the table in blocks of eight l-steps per segment, with the signs of the rescaled recurrence
+    // (kernels.h); blocks of padding at the end: the kernels load ahead
+    int nblocks = 0;
+    for (int si = 0; si < pl->seg.n; ++si) {
+        pl->seg.b0[si] = nblocks;
+        nblocks += (pl->seg.s1[si] + 7) / 8 - pl->seg.s0[si] / 8;
+    }
+    auto sign = [](int l) { return (l & 2) ? -1.0 : 1.0; };
+    pl->kstride = nblocks * 16 * K;
+    std::vector<double> kb2((size_t)L * pl->kstride + kWigAhead * 16 * K, 0.0);
     for (int mp = 0; mp < L; ++mp)
-        for (int l = 0; l < L; ++l) {
-            int si = 0;
-            while (pl->seg.s1[si] <= l) ++si;
+        for (int si = 0; si < pl->seg.n; ++si) {
             const int js[2] = {pl->seg.je[si], pl->seg.jo[si]};
-            for (int s = 0; s < 2; ++s) {
-                if (js[s] < 0) continue;
-                const double kap = t.kappa[(size_t)js[s] * L + l];
-                // h_l(m') of the rescaled recurrence folded in (the g_l(m) side goes with f_lm)
-                const double hh = dt.h[(size_t)mp * L + l];
-                for (int k = 0; k < K; ++k)
-                    kb2[(((size_t)mp * L + l) * 2 + s) * K + k] =
-                        kap * t.sig[(size_t)l * K + k] * ncol[((size_t)mp * L + l) * K + k] * hh;
-            }
+            for (int l = pl->seg.s0[si]; l < pl->seg.s1[si]; ++l)
+                for (int s = 0; s < 2; ++s) {
+                    if (js[s] < 0) continue;
+                    const double kap = t.kappa[(size_t)js[s] * L + l];
+                    // h_l(m') of the rescaled recurrence folded in (the g_l(m) side goes with f_lm)
+                    const double hh = sign(l) * dt.h[(size_t)mp * L + l];
+                    const size_t rec = (size_t)mp * pl->kstride + (size_t)pl->seg.b0[si] * 16 * K +
+                                       (size_t)(l - pl->seg.s0[si] / 8 * 8) * 2 * K;
+                    for (int k = 0; k < K; ++k)
+                        kb2[rec + s * K + k] = kap * t.sig[(size_t)l * K + k] * ncol[((size_t)mp * L + l) * K + k] * hh;
+                }
+        }
+    // u in the same blocks
+    pl->ustride = nblocks * 8;
+    std::vector<double> urow((size_t)L * pl->ustride + kWigAhead * 8, 0.0);
+    for (int mp = 0; mp < L; ++mp)
+        for (int si = 0; si < pl->seg.n; ++si) {
+            const int lb0 = pl->seg.s0[si] / 8 * 8, lb1 = std::min((pl->seg.s1[si] + 7) / 8 * 8, L);
+            for (int l = lb0; l < lb1; ++l)
+                urow[(size_t)mp * pl->ustride + (size_t)pl->seg.b0[si] * 8 + (l - lb0)] =
+                    ((l & 1) ? 1.0 : -1.0) * dt.ut[(size_t)mp * L + l];
+        }
+    std::vector<WigSeg> segs(pl->seg.n + 2, WigSeg{});
+    for (int si = 0; si < pl->seg.n; ++si) {
+        const SegTab &g = pl->seg;
+        const int je = g.je[si], jo = g.jo[si];
+        const int jen = si + 1 < g.n ? g.je[si + 1] : -1, jon = si + 1 < g.n ? g.jo[si + 1] : -1;
+        WigSeg &r = segs[si];
+        r.s0 = g.s0[si];
+        r.s1 = g.s1[si];
+        auto set = [&](int j, int &Lj, long long &o) {
+            Lj = j >= 0 ? pl->sc.Lj[j] : 0;
+            o = j >= 0 ? pl->sc.off[j] : 0;
+        };
+        set(je != jen ? je : -1, r.Le, r.offe);
+        set(jo != jon ? jo : -1, r.Lo, r.offo);
+        set(je, r.Lae, r.offae);
+        set(jo, r.Lao, r.offao);
+        r.newe = si == 0 || je != g.je[si - 1];
+        r.newo = si == 0 || jo != g.jo[si - 1];
+    }
+    // the per-lane arrays by table row
+    pl->rows = nblocks * 8;
+    std::vector<int> rowl(pl->rows, -1);
+    std::vector<double> prow((size_t)(pl->rows + 8 * kWigAhead) * Lp, 0.0);
+    for (int si = 0; si < pl->seg.n; ++si) {
+        const int lb0 = pl->seg.s0[si] / 8 * 8, lb1 = std::min((pl->seg.s1[si] + 7) / 8 * 8, L);
+        for (int l = lb0; l < lb1; ++l) {
+            const size_t row = (size_t)pl->seg.b0[si] * 8 + (l - lb0);
+            if (l >= pl->seg.s0[si] && l < pl->seg.s1[si]) rowl[row] = l;
+            std::copy_n(&dt.pt[(size_t)l * Lp], Lp, &prow[row * Lp]);
+        }
+    }
+    for (int mp = 0; mp < L; ++mp)
+        for (int m = 0; m < L; ++m) {
+            dt.seedt[(size_t)mp * Lp + m] *= sign(std::max(mp, m));
+            dt.seedtm[(size_t)mp * Lp + m] *= sign(std::max(mp, m));
         }
     Plan &P = *pl;
     const int M = 2 * L - 1;
@@ -617,14 +712,13 @@ int build_plan(int kind, int L, int N, double lam, int J_min, int grid, Plan *&o
                                      : (2.0 * l + 1.0) / (8.0 * M_PI * M_PI);
     P.n_kb2 = kb2.size();
     P.n_tg = tgf.size();
-    dt.ut.resize(dt.ut.size() + 1, 0.0);  // one padding entry (as for kb2)
-    bool ok = upload(P, P.pq, dt.pt) && upload(P, P.uv, dt.ut) && upload(P, P.gsc, dt.g) && upload(P, P.kb2, kb2) &&
+    bool ok = upload(P, P.pq, prow) && upload(P, P.uv, urow) && upload(P, P.gsc, dt.g) && upload(P, P.kb2, kb2) &&
               upload(P, P.seed, dt.seedt) && upload(P, P.seedm, dt.seedtm) && upload(P, P.seede, dt.seedte) &&
-              upload(P, P.tgf, tgf) && upload(P, P.tga, tga) && upload(P, P.fac, fac) && upload(P, P.phi, t.phi);
+              upload(P, P.tgf, tgf) && upload(P, P.tga, tga) && upload(P, P.fac, fac) && upload(P, P.phi, t.phi) && upload(P, P.rowl, rowl) && upload(P, P.segs, segs);
     if (!ok) return S2DW_E_NOMEM;
     // tiles
     P.seede_h = dt.seedte;
-    int rc_t = set_slots(P, wig_slots(K));
+    int rc_t = set_slots(P, 0, true);
     if (rc_t != S2DW_OK) return rc_t;
     // Bluestein chirp spectra per scale, for the scale's grid band-limit Lg (T = 2Lg - 1;
     // see stages.hip for the convolution layouts)
@@ -788,7 +882,7 @@ int build_plan(int kind, int L, int N, double lam, int J_min, int grid, Plan *&o
     // workspaces
     int maxLj = 0;
     for (int j = 0; j < t.S; ++j) maxLj = std::max(maxLj, P.sc.Lj[j]);
-    P.s_fpad = (size_t)L * Lp;
+    P.s_fpad = (size_t)(P.rows + 8 * kWigAhead) * Lp;
     P.s_U = (size_t)std::max<int64_t>(off, 1);
     P.s_Ub = (size_t)t.N * P.nb * std::max(maxLj, 1);
     P.s_Y = (size_t)P.Nh * P.nb * M;
@@ -1006,8 +1100,8 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     const int L = P.L;
     {
         Stage sg("pad", st);
-        if (cx) S2DW_CHECK_HIP(launch_pad_flm_complex(flm, P.gsc, w.fpad, L, P.Lp, P.s_fpad, maps / 2, st));
-        else S2DW_CHECK_HIP(launch_pad_flm(flm, P.gsc, w.fpad, L, P.Lp, P.s_fpad, maps, st));
+        if (cx) S2DW_CHECK_HIP(launch_pad_flm_complex(flm, P.gsc, P.rowl, P.rows, w.fpad, L, P.Lp, P.s_fpad, maps / 2, st));
+        else S2DW_CHECK_HIP(launch_pad_flm(flm, P.gsc, P.rowl, P.rows, w.fpad, L, P.Lp, P.s_fpad, maps, st));
     }
     WigFwdArgs a{};
     a.fpad = w.fpad;
@@ -1020,18 +1114,22 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     a.U = w.U;
     a.s_fpad = P.s_fpad;
     a.s_U = P.s_U;
+    a.kstride = P.kstride;
+    a.ustride = P.ustride;
     a.L = L;
     a.Lp = P.Lp;
     a.N = P.ht.N;
     a.eoff = P.eoff;
-    for (int k = 0; k < P.K; ++k) a.nk[k] = P.ht.nk[k];
-    a.seg = P.seg;
-    a.sc = P.sc;
+    a.segs = P.segs;
     {
         Stage sg("wigner_fwd", st);
-        a.tiles = sh.tiles_fwd;
-        a.nplain = sh.nfwd_plain;
-        S2DW_CHECK_HIP(launch_wig_fwd(a, P.K, sh.R, sh.nfwd_plain + sh.nfwd_x, maps, st));
+        const int want = sh.nfwd > 1 ? wig_fwd_slots_for(P.K, (long)(P.Lp / 64) * L * maps) : sh.fwd[0].R;
+        const Shape::Fwd *ft = &sh.fwd[0];
+        for (int i = 1; i < sh.nfwd; ++i)
+            if (sh.fwd[i].R == want) ft = &sh.fwd[i];
+        a.tiles = ft->tiles;
+        a.nplain = ft->nplain;
+        S2DW_CHECK_HIP(launch_wig_fwd(a, P.K, ft->R, ft->nplain + ft->nx, maps, st));
     }
     const int N = P.ht.N;
     const size_t per_map = P.woff[P.S];  // elements of one W (complex ones with cx)
@@ -1341,22 +1439,24 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
     a.V = w.U;
     a.Fpart = w.Fpart;
     a.s_V = P.s_U;
-    a.s_F = sh.s_F;
+    const Shape::Adj &at = sh.adj[f32];
+    a.s_F = at.s_F;
+    a.kstride = P.kstride;
+    a.ustride = P.ustride;
     a.L = L;
     a.Lp = P.Lp;
-    a.group = sh.group;
+    a.group = at.group;
     a.f32 = f32;
-    a.seg = P.seg;
-    a.sc = P.sc;
+    a.segs = P.segs;
     {
         Stage sg("wigner_adj", st);
-        a.tiles = sh.tiles_adj;
-        a.nplain = sh.nadj_plain;
-        S2DW_CHECK_HIP(launch_wig_adj(a, P.K, sh.R, sh.nadj_plain + sh.nadj_x, maps, st));
+        a.tiles = at.tiles;
+        a.nplain = at.nplain;
+        S2DW_CHECK_HIP(launch_wig_adj(a, P.K, at.R, at.nplain + at.nx, maps, st));
     }
     {
         Stage sg("syn_final", st);
-        S2DW_CHECK_HIP(launch_syn_final(w.Fpart, sh.s_F, f32, sh.nblk, sh.group, P.Lmax, P.fac, P.gsc, wphi, P.phi, flm,
+        S2DW_CHECK_HIP(launch_syn_final(w.Fpart, at.s_F, f32, at.nblk, at.group, P.Lmax, P.fac, P.gsc, wphi, P.phi, flm,
                                         L, P.Lp, maps, st));
     }
     return S2DW_OK;
@@ -1422,23 +1522,16 @@ int persist_shape(Plan &P, Shape &sh) {
         ts.nfwd_x = (int)x_a.size();
         ts.nadj_plain = (int)pl_s.size();
         ts.nadj_x = (int)x_s.size();
-        pl_a.insert(pl_a.end(), x_a.begin(), x_a.end());
-        pl_s.insert(pl_s.end(), x_s.begin(), x_s.end());
-        if (!upload(P, ts.fwd, pl_a) || !upload(P, ts.adj, pl_s)) return S2DW_E_NOMEM;
+        if (!upload(P, ts.fwd, with_starts(P, pl_a, x_a)) || !upload(P, ts.adj, with_starts(P, pl_s, x_s)))
+            return S2DW_E_NOMEM;
         it = P.tilesets.emplace(key, ts).first;
     }
     const Plan::TileSet &ts = it->second;
     sh = P.cur;
-    sh.R = R;
-    sh.tiles_fwd = ts.fwd;
-    sh.tiles_adj = ts.adj;
-    sh.nfwd_plain = ts.nfwd_plain;
-    sh.nfwd_x = ts.nfwd_x;
-    sh.nadj_plain = ts.nadj_plain;
-    sh.nadj_x = ts.nadj_x;
-    sh.group = 4 * R;
-    sh.nblk = (P.L + sh.group - 1) / sh.group;
-    sh.s_F = (size_t)sh.nblk * P.L * P.Lp;
+    sh.nfwd = 1;
+    sh.fwd[0] = {R, ts.fwd, ts.nfwd_plain, ts.nfwd_x};
+    const int group = 4 * R, nblk = (P.L + group - 1) / group;
+    sh.adj[0] = sh.adj[1] = {R, group, nblk, ts.adj, ts.nadj_plain, ts.nadj_x, (size_t)nblk * P.L * P.Lp};
     sh.fuse = 0;
     return S2DW_OK;
 }
@@ -1460,10 +1553,10 @@ int build_program(PProgram &pr, int dir, int f32, const std::vector<PGroup> &gs,
         if (!w) return S2DW_E_NOMEM;
         const size_t n = (size_t)gs[g].count;
         if (!walloc(*w, w->fpad, n * P.s_fpad) || !walloc(*w, w->U, n * P.s_U) || !walloc(*w, w->Ub, n * P.s_Ub) ||
-            !walloc(*w, w->Y, n * P.s_Y) || !walloc(*w, w->Fpart, n * sh.s_F))
+            !walloc(*w, w->Y, n * P.s_Y) || !walloc(*w, w->Fpart, n * sh.s_F()))
             return S2DW_E_NOMEM;
         w->cap = gs[g].count;
-        w->s_F = sh.s_F;
+        w->s_F = sh.s_F();
         Recorder R;
         t_rec = &R;
         t_no_events = true;
@@ -1668,13 +1761,19 @@ int run_persistent(int dir, const s2dw_group *groups, int32_t ngroups, int32_t *
 
 namespace s2dw {
 
+// The padded f_lm takes the Wigner stage's table rows instead of L rows: at most 8 rows per
+// segment (kMaxSegs at most, two segments per scale) more, and those read ahead.  The size a call
+// may take is still that of L rows within S2DW_NOALLOC_SCRATCH_BYTES, which keeps Lp below 768, and
+// 512 for the two maps of a complex signal: these bytes hold the extra rows.
+constexpr size_t kScratchRows = 8ull << 20;
+
 // Fixed device scratch of s2dw_analysis_noalloc (the stage workspaces of one call): one copy
 // per GPU, held until the process ends.  In host code the name is only a stand-in for the
 // device symbol; its device address comes from hipGetSymbolAddress (per device, below).
 // File-scope array with external linkage: a `static` one keeps a local binding in the
 // device code object, outside its dynamic symbol table, and the runtime cannot resolve
 // it by name.
-__device__ __align__(256) double2 scratch[S2DW_NOALLOC_SCRATCH_BYTES / sizeof(double2)];
+__device__ __align__(256) double2 scratch[(S2DW_NOALLOC_SCRATCH_BYTES + kScratchRows) / sizeof(double2)];
 
 namespace {
 
@@ -1782,7 +1881,7 @@ int s2dw_analysis_batched(const s2dw_params *p, int32_t count, const double *flm
     const Shape sh = shape_of(*P);
     const int chunk = std::max(1, std::min<int>(count, sh.chunk / per));
     Work *w = nullptr;
-    rc = get_work(*P, st, chunk * per, sh.s_F, w);
+    rc = get_work(*P, st, chunk * per, sh.s_F(), w);
     if (rc != S2DW_OK) return rc;
     const size_t L2 = (size_t)p->L * p->L;
     const size_t wmap = P->woff[P->S] * (f32 ? 4 : 8) * per;
@@ -1815,7 +1914,7 @@ int s2dw_synthesis_batched(const s2dw_params *p, int32_t count, const void *W, c
     const Shape sh = shape_of(*P);
     const int chunk = std::max(1, std::min<int>(count, sh.chunk / per));
     Work *w = nullptr;
-    rc = get_work(*P, st, chunk * per, sh.s_F, w);
+    rc = get_work(*P, st, chunk * per, sh.s_F(), w);
     if (rc != S2DW_OK) return rc;
     const size_t L2 = (size_t)p->L * p->L;
     const size_t wmap = P->woff[P->S] * (f32 ? 4 : 8) * per;
@@ -1891,7 +1990,7 @@ int s2dw_autotune(const s2dw_params *p, int32_t count, void *stream, int32_t *sl
     };
     int Ropt[3];
     const int nR = wig_slot_options(P->K, Ropt);
-    int bestR = shape_of(*P).R, bestC = cmax, bestF = 1;
+    int bestR = shape_of(*P).adj[f32].R, bestC = cmax, bestF = 1;
     double best = 1e30;
     for (int i = 0; i < nR && rc == S2DW_OK; ++i) {
         double sec = 0;
@@ -1968,7 +2067,7 @@ int s2dw_get_tuning(const s2dw_params *p, int32_t *slots, int32_t *chunk, int32_
     rc = get_plan(kWavelet, p->L, p->N, p->lambda, p->J_min, P, p->precision == S2DW_MIXED, p->grid);
     if (rc != S2DW_OK) return rc;
     const Shape sh = shape_of(*P);
-    if (slots) *slots = sh.R;
+    if (slots) *slots = sh.adj[p->precision == S2DW_MIXED ? 1 : 0].R;
     if (chunk) *chunk = sh.chunk;
     if (fuse) *fuse = sh.fuse;
     return S2DW_OK;
@@ -2000,7 +2099,7 @@ int s2dw_workspace_bytes(const s2dw_params *p, int32_t count, uint64_t *bytes) {
     rc = get_plan(kWavelet, p->L, p->N, p->lambda, p->J_min, P, p->precision == S2DW_MIXED, p->grid);
     if (rc != S2DW_OK) return rc;
     const Shape sh = shape_of(*P);
-    const uint64_t per_map = 16ull * (P->s_fpad + P->s_U + P->s_Ub + P->s_Y + sh.s_F);
+    const uint64_t per_map = 16ull * (P->s_fpad + P->s_U + P->s_Ub + P->s_Y + sh.s_F());
     const int per = p->reality == 0 ? 2 : 1;  // real maps per signal
     *bytes = per_map * per * (uint64_t)std::min<int>(count, std::max(sh.chunk / per, 1));
     return S2DW_OK;
@@ -2032,7 +2131,7 @@ int s2dw_analysis_noalloc(const s2dw_params *p, const double *flm, void *W, doub
     if (!P) return S2DW_E_ARG;  // the plan must have been built by an allocating call
     const bool cx = p->reality == 0;
     const int per = cx ? 2 : 1;  // real maps of the signal
-    const size_t per_map = P->s_fpad + P->s_U + P->s_Ub + P->s_Y;  // complex elements
+    const size_t per_map = (size_t)P->L * P->Lp + P->s_U + P->s_Ub + P->s_Y;  // complex elements
     if ((size_t)per * per_map * sizeof(double2) > S2DW_NOALLOC_SCRATCH_BYTES) return S2DW_E_UNSUPPORTED;
     double2 *base = nullptr;
     rc = scratch_of_current_device(base);
@@ -2069,7 +2168,7 @@ int s2dw_scaling(const s2dw_params *p, const double *flm, double *Wphi_lm, doubl
     if (rc != S2DW_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     Work *w = nullptr;
-    rc = get_work(*P, st, 1, shape_of(*P).s_F, w);
+    rc = get_work(*P, st, 1, shape_of(*P).s_F(), w);
     if (rc != S2DW_OK) return rc;
     double2 *wphi = (double2 *)Wphi_lm;
     if (!wphi) wphi = w->fpad;  // scratch: L*Lp >= L*L complex
@@ -2080,7 +2179,7 @@ int s2dw_scaling(const s2dw_params *p, const double *flm, double *Wphi_lm, doubl
         if (rc != S2DW_OK) return rc;
         Work *wq = nullptr;
         const Shape shq = shape_of(*Q);
-        rc = get_work(*Q, st, 1, shq.s_F, wq);
+        rc = get_work(*Q, st, 1, shq.s_F(), wq);
         if (rc != S2DW_OK) return rc;
         rc = run_inverse(*Q, shq, *wq, 1, wphi, Wphi_map, 0, st);
     }
@@ -2141,7 +2240,7 @@ int s2dw_sht_forward(const s2dw_params *p, const double *f_map, double *flm, voi
     if (rc != S2DW_OK) return rc;
     Work *w = nullptr;
     const Shape sh = shape_of(*Q);
-    rc = get_work(*Q, (hipStream_t)stream, 1, sh.s_F, w);
+    rc = get_work(*Q, (hipStream_t)stream, 1, sh.s_F(), w);
     if (rc != S2DW_OK) return rc;
     return run_forward(*Q, sh, *w, 1, f_map, nullptr, (double2 *)flm, 0, (hipStream_t)stream);
 }
@@ -2154,7 +2253,7 @@ int s2dw_sht_inverse(const s2dw_params *p, const double *flm, double *f_map, voi
     if (rc != S2DW_OK) return rc;
     Work *w = nullptr;
     const Shape sh = shape_of(*Q);
-    rc = get_work(*Q, (hipStream_t)stream, 1, sh.s_F, w);
+    rc = get_work(*Q, (hipStream_t)stream, 1, sh.s_F(), w);
     if (rc != S2DW_OK) return rc;
     return run_inverse(*Q, sh, *w, 1, (const double2 *)flm, f_map, 0, (hipStream_t)stream);
 }

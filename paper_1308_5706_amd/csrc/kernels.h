@@ -10,25 +10,33 @@ namespace s2dw {
 constexpr int kAdjWaves = 8;                 // waves per synthesis Wigner workgroup
 constexpr int kAdjThreads = kAdjWaves * 64;
 
+constexpr int kWigAhead = 6;                 // table blocks read ahead, at most
+
 struct WigFwdArgs {
     // The l-recurrence runs on D_l = Delta^l_{m'm} / (g_l(m) h_l(m')) (rescaled so that its
     // Delta^{l-1} coefficient is 1: D_{l+1} = -(ut_l(m') pt_l(m)) D_l - D_{l-1}); g goes with
-    // f_lm and h with the kb2 table.
-    const double2 *fpad;   // [L][Lp]   g_l(m) f_lm for m <= l (0 elsewhere)
-    const double *pq;      // [L][Lp]   pt_l(m)
-    const double *uv;      // [Lp][L]   ut_l(m')
-    const double *kb2;     // [Lp][L][2][K]  kappa^{j(slot,l)}(l) sigma_{l,n_k} Delta^l_{m' n_k} h_l(m')
-    const double *seed;    // [Lp][Lp]  D at l0 = max(m',m)
+    // f_lm and h with the kb2 table.  With the signs s_l = +, +, -, - (l mod 4) on D the
+    // recurrence is a sum, s_{l+1} D_{l+1} = s_{l-1} D_{l-1} + u_l(m') pt_l(m) s_l D_l, u_l = -ut_l
+    // for even l and ut_l for odd l; kb2 and the start values carry s_l.
+    // Per-lane arrays by table row, row 8 b + s for step s of table block b (see kb2), and kWigAhead
+    // blocks of rows beyond the last (read ahead, as are the tables).
+    const double2 *fpad;   // [rows][Lp]  g_l(m) f_lm for m <= l (0 elsewhere, and for an l outside the segment)
+    const double *pq;      // [rows][Lp]  pt_l(m)
+    const double *uv;      // rows of ustride: u_l(m') in the same blocks as kb2, zero from L on
+    // rows m' of kstride values, table blocks of 8 l-steps: [8][2][K] s_l kappa^{j(slot,l)}(l)
+    // sigma_{l,n_k} Delta^l_{m' n_k} h_l(m').  Segment si of SegTab takes the blocks from seg.b0[si] on, at
+    // l = 8 floor(s0/8), ..; steps of a block outside the segment hold zeros.
+    const double *kb2;
+    const double *seed;    // [Lp][Lp]  D at l0 = max(m',m) (with the sign)
     const double *seedm;   // [Lp][Lp]  its mantissa (extended-exponent variant)
     const int *seede;      // [Lp][Lp]  its exponent
-    const int2 *tiles;     // (m0, m'0) per workgroup
+    const int4 *tiles;     // per workgroup: m0, m'0, and the segment and table block of l = max(m0, m'0)
+    const WigSeg *segs;    // the segments' records (SegTab)
     int nplain;            // workgroups [0, nplain) take plain tiles, the rest extended-exponent ones
     double2 *U;            // workspace; scale j at sc.off[j]: [N][Lj][Lj] = [n][m][m']
     size_t s_fpad, s_U;    // per-map strides (elements) of a batch; map = blockIdx.y
+    int kstride, ustride;
     int L, Lp, N, eoff;    // eoff = 3 when eta_N = i (conj(eta) = i^3), else 0
-    int nk[kMaxK];
-    SegTab seg;
-    ScaleTab sc;
 };
 
 struct WigAdjArgs {
@@ -38,17 +46,19 @@ struct WigAdjArgs {
     const double *seed;
     const double *seedm;
     const int *seede;
-    const int2 *tiles;
+    const int4 *tiles;
+    const WigSeg *segs;
     int nplain;
     const void *V;         // scale j at sc.off[j]: [K][2][Lj][Lj] = [k][P|Q][m][m'], double2 or float2
     void *Fpart;           // [L / group][L][Lp] partial sums over each m' group, double2 or float2
     size_t s_V, s_F;       // per-map strides (complex elements) of a batch; map = blockIdx.y
+    int kstride, ustride;
     int L, Lp, group, f32;
-    SegTab seg;
-    ScaleTab sc;
 };
 
-int wig_slots(int K);                        // default m' slots per wave for K carried orders
+// Default m' slots per wave for K carried orders and `waves` waves at one slot per wave.
+int wig_fwd_slots_for(int K, long waves);
+int wig_adj_slots(int K, long waves, int f32);
 int wig_slot_options(int K, int *R);          // compiled slot counts for K (up to 3), returns how many
 hipError_t launch_wig_fwd(const WigFwdArgs &a, int K, int R, int ntiles, int maps, hipStream_t st);
 hipError_t launch_wig_adj(const WigAdjArgs &a, int K, int R, int ntiles, int maps, hipStream_t st);
@@ -174,13 +184,14 @@ hipError_t launch_gamma_adj_cx(const GammaArgs &a, int cmaps, hipStream_t st);
 
 // maps: number of maps of a batch (grid z); f_lm, W^Phi_lm of map i at i L^2, workspaces at i s_*.
 // The padded copy carries the factor g_l(m) ([L][Lp]) of the rescaled Wigner recurrence.
-hipError_t launch_pad_flm(const double2 *flm, const double *g, double2 *fpad, int L, int Lp, size_t s_fpad, int maps,
-                          hipStream_t st);
+// rowl [rows]: the l of each row of fpad, or -1 for a row of zeros.
+hipError_t launch_pad_flm(const double2 *flm, const double *g, const int *rowl, int rows, double2 *fpad, int L, int Lp,
+                          size_t s_fpad, int maps, hipStream_t st);
 hipError_t launch_scaling(const double2 *flm, const double *phi, double2 *wphi, int L, int maps, hipStream_t st);
 // Complex signals as two real ones: cmaps complex f_lm -> real maps 2z, 2z + 1 of fpad, and
 // back: f = a + i b (+ the scaling part) from the syntheses of those maps (each L^2 at k s_fab).
-hipError_t launch_pad_flm_complex(const double2 *flm, const double *g, double2 *fpad, int L, int Lp, size_t s_fpad,
-                                  int cmaps, hipStream_t st);
+hipError_t launch_pad_flm_complex(const double2 *flm, const double *g, const int *rowl, int rows, double2 *fpad, int L,
+                                  int Lp, size_t s_fpad, int cmaps, hipStream_t st);
 hipError_t launch_merge_complex(const double2 *fab, size_t s_fab, const double2 *wphi, const double *phi,
                                 double2 *flm, int L, int cmaps, hipStream_t st);
 // g: the factor g_l(m) ([L][Lp]) the partial sums of the rescaled recurrence lack.
@@ -218,6 +229,7 @@ constexpr int kPersistMaxP = 2048;  // largest transform of the executor (P / 8 
 struct PadArgs {
     const double2 *flm;
     const double *g;
+    const int *rowl;
     double2 *fpad;
     int L, Lp;
     size_t s_fpad;

@@ -8,14 +8,17 @@ namespace s2dw {
 
 // Batched small kernels: map = blockIdx.z; f_lm and W^Phi_lm of map i start at i L^2.
 // fpad = g_l(m) f_lm, m <= l: the Wigner stage's rescaled recurrence takes the factor g here.
-__global__ void pad_flm_kernel(const double2 *flm, const double *g, double2 *fpad, int L, int Lp, size_t s_fpad) {
-    pad_flm_elem(flm, g, fpad, L, Lp, s_fpad, blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, blockIdx.z);
+__global__ void pad_flm_kernel(const double2 *flm, const double *g, const int *rowl, double2 *fpad, int L, int Lp,
+                               size_t s_fpad) {
+    pad_flm_elem(flm, g, rowl, fpad, L, Lp, s_fpad, blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, blockIdx.z);
 }
 
-hipError_t launch_pad_flm(const double2 *flm, const double *g, double2 *fpad, int L, int Lp, size_t s_fpad, int maps,
-                          hipStream_t st) {
-    if (t_rec) return rec_job(pkind(PS_PAD, 0), (long long)((Lp + 255) / 256) * L, maps, 256, PadArgs{flm, g, fpad, L, Lp, s_fpad});
-    hipLaunchKernelGGL(pad_flm_kernel, dim3((Lp + 255) / 256, L, maps), dim3(256), 0, st, flm, g, fpad, L, Lp,
+hipError_t launch_pad_flm(const double2 *flm, const double *g, const int *rowl, int rows, double2 *fpad, int L, int Lp,
+                          size_t s_fpad, int maps, hipStream_t st) {
+    if (t_rec)
+        return rec_job(pkind(PS_PAD, 0), (long long)((Lp + 255) / 256) * rows, maps, 256,
+                       PadArgs{flm, g, rowl, fpad, L, Lp, s_fpad});
+    hipLaunchKernelGGL(pad_flm_kernel, dim3((Lp + 255) / 256, rows, maps), dim3(256), 0, st, flm, g, rowl, fpad, L, Lp,
                        s_fpad);
     return hipGetLastError();
 }
@@ -24,13 +27,13 @@ hipError_t launch_pad_flm(const double2 *flm, const double *g, double2 *fpad, in
 // a batch becomes real maps 2z (the real part of f on the sphere) and 2z + 1 (the imaginary
 // part), since Eq. 1 is linear in f.  Their coefficients, for 0 <= m <= l, are
 //   a_lm = (f_lm + (-1)^m conj f_{l,-m}) / 2,   b_lm = (f_lm - (-1)^m conj f_{l,-m}) / (2i).
-__global__ void pad_flm_complex_kernel(const double2 *flm, const double *g, double2 *fpad, int L, int Lp,
-                                       size_t s_fpad) {
+__global__ void pad_flm_complex_kernel(const double2 *flm, const double *g, const int *rowl, double2 *fpad, int L,
+                                       int Lp, size_t s_fpad) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    const int l = blockIdx.y;
     if (m >= Lp) return;
+    const int l = rowl[blockIdx.y];
     flm += (size_t)blockIdx.z * L * L;
-    double2 *pa = fpad + (size_t)(2 * blockIdx.z) * s_fpad + (size_t)l * Lp + m;
+    double2 *pa = fpad + (size_t)(2 * blockIdx.z) * s_fpad + (size_t)blockIdx.y * Lp + m;
     double2 *pb = pa + s_fpad;
     if (m > l) {
         *pa = make_double2(0.0, 0.0);
@@ -45,11 +48,11 @@ __global__ void pad_flm_complex_kernel(const double2 *flm, const double *g, doub
     *pb = make_double2(c * (f.y - ci), -c * (f.x - cr));
 }
 
-hipError_t launch_pad_flm_complex(const double2 *flm, const double *g, double2 *fpad, int L, int Lp, size_t s_fpad,
-                                  int cmaps, hipStream_t st) {
+hipError_t launch_pad_flm_complex(const double2 *flm, const double *g, const int *rowl, int rows, double2 *fpad, int L,
+                                  int Lp, size_t s_fpad, int cmaps, hipStream_t st) {
     if (t_rec) return hipErrorNotSupported;
-    hipLaunchKernelGGL(pad_flm_complex_kernel, dim3((Lp + 255) / 256, L, cmaps), dim3(256), 0, st, flm, g, fpad, L,
-                       Lp, s_fpad);
+    hipLaunchKernelGGL(pad_flm_complex_kernel, dim3((Lp + 255) / 256, rows, cmaps), dim3(256), 0, st, flm, g, rowl, fpad,
+                       L, Lp, s_fpad);
     return hipGetLastError();
 }
 

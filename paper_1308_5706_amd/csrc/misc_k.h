@@ -6,11 +6,13 @@
 
 namespace s2dw {
 
-// fpad = g_l(m) f_lm for m <= l (zero for l < m < Lp): the Wigner stage's rescaled recurrence
-// takes the factor g here.  Element (m, l) of map z; f_lm of map z starts at z L^2.
-__device__ __forceinline__ void pad_flm_elem(const double2 *flm, const double *g, double2 *fpad, int L, int Lp,
-                                             size_t s_fpad, int m, int l, int z) {
+// fpad = g_l(m) f_lm for m <= l (zero for l < m < Lp), l = rowl[row] (a row of zeros where it is
+// -1): the Wigner stage's rescaled recurrence takes the factor g here.  Element (row, m) of map
+// z; f_lm of map z starts at z L^2.
+__device__ __forceinline__ void pad_flm_elem(const double2 *flm, const double *g, const int *rowl, double2 *fpad, int L,
+                                             int Lp, size_t s_fpad, int m, int row, int z) {
     if (m >= Lp) return;
+    const int l = rowl[row];
     flm += (size_t)z * L * L;
     fpad += (size_t)z * s_fpad;
     double2 v = make_double2(0.0, 0.0);
@@ -19,7 +21,7 @@ __device__ __forceinline__ void pad_flm_elem(const double2 *flm, const double *g
         const double c = g[(size_t)l * Lp + m];
         v = make_double2(c * f.x, c * f.y);
     }
-    fpad[(size_t)l * Lp + m] = v;
+    fpad[(size_t)row * Lp + m] = v;
 }
 
 // W^Phi_lm = sqrt(4 pi/(2l+1)) f_lm Phi_l0 (Eq. 31); Phi is real.  Element l^2 + m of map z.

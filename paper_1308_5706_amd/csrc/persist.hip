@@ -53,11 +53,15 @@ constexpr int kMaxNH = 4;                          // orders n >= 0 of the direc
 constexpr int kVmcnt0 = 0x0F70;                    // s_waitcnt vmcnt(0) (gfx9 encoding; expcnt, lgkmcnt not waited)
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-// LDS of a worker: the FFT columns (256 threads' worth: padded(2048) elements of the largest
-// complex type), the synthesis Wigner window, the direct fused passes' tables
-constexpr int kPersistLds =
-    cmax(cmax(fft::padded(kPersistMaxP) * (int)sizeof(double2), kPersistAW * 8 * 64 * 2 * (int)sizeof(double)),
-         cmax(kAlphaGammaCoeffs * (int)sizeof(double2), (kMaxNH + 2) * 256 * (int)sizeof(double2)));
+// LDS of a worker of the separation-of-variables part: the FFT columns (256 threads' worth: padded(2048) elements of the largest
+// complex type), the direct fused passes' tables
+constexpr int kPersistLds = cmax(fft::padded(kPersistMaxP) * (int)sizeof(double2),
+                                 cmax(kAlphaGammaCoeffs * (int)sizeof(double2), (kMaxNH + 2) * 256 * (int)sizeof(double2)));
+// LDS of a worker of the Wigner part (its tile shapes, below)
+constexpr int kPersistFwdLds = cmax(cmax((int)sizeof(WigFwdLds<1, 4>), (int)sizeof(WigFwdLds<2, 2>)),
+                                    cmax((int)sizeof(WigFwdLds<3, 2>), (int)sizeof(WigFwdLds<4, 2>)));
+constexpr int kPersistAdjLds = cmax(cmax((int)sizeof(WigAdjLds<1, 4, double, kPersistAW>), (int)sizeof(WigAdjLds<2, 2, double, kPersistAW>)),
+                                    cmax((int)sizeof(WigAdjLds<3, 2, double, kPersistAW>), (int)sizeof(WigAdjLds<4, 2, double, kPersistAW>)));
 
 // The argument block of a job, read through the constant address space (as kernel
 // arguments are): the loads are scalar and may be repeated wherever the compiler likes.
@@ -112,14 +116,14 @@ __device__ __forceinline__ void persist_item(int kind, const unsigned char *ap, 
             case PS_PAD: {
                 const PadArgs &p = job_args<PadArgs>(ap);
                 const int gx0 = (p.Lp + 255) / 256;
-                pad_flm_elem(p.flm, p.g, p.fpad, p.L, p.Lp, p.s_fpad, (vb0 % gx0) * 256 + tid, vb0 / gx0, by);
+                pad_flm_elem(p.flm, p.g, p.rowl, p.fpad, p.L, p.Lp, p.s_fpad, (vb0 % gx0) * 256 + tid, vb0 / gx0, by);
                 break;
             }
             case PS_WIGF: {
                 const WigFwdArgs &a = job_args<WigFwdArgs>(ap);
 #define S2DW_WF(K, R)                                                     \
-    if (vb0 < a.nplain) wig_fwd_body<K, R, false>(a, vb0, by, tid);       \
-    else wig_fwd_body<K, R, true>(a, vb0, by, tid);
+    if (vb0 < a.nplain) wig_fwd_body<K, R, false>(a, (WigFwdLds<K, R> *)lds, vb0, by, tid); \
+    else wig_fwd_body<K, R, true>(a, (WigFwdLds<K, R> *)lds, vb0, by, tid);
                 S2DW_PERSIST_KR(S2DW_WF)
 #undef S2DW_WF
                 break;
@@ -267,10 +271,9 @@ __device__ __forceinline__ void persist_item(int kind, const unsigned char *ap, 
             case PS_WIGA: {
                 using VT = real_t<C>;
                 const WigAdjArgs &a = job_args<WigAdjArgs>(ap);
-                VT *win = (VT *)lds;
-#define S2DW_WA(K, R)                                                                          \
-    if (vb0 < a.nplain) wig_adj_body<K, R, false, VT, kPersistAW>(a, win, vb0, by, tid);       \
-    else wig_adj_body<K, R, true, VT, kPersistAW>(a, win, vb0, by, tid);
+#define S2DW_WA(K, R)                                                                                                  \
+    if (vb0 < a.nplain) wig_adj_body<K, R, false, VT, kPersistAW>(a, (WigAdjLds<K, R, VT, kPersistAW> *)lds, vb0, by, tid); \
+    else wig_adj_body<K, R, true, VT, kPersistAW>(a, (WigAdjLds<K, R, VT, kPersistAW> *)lds, vb0, by, tid);
                 S2DW_PERSIST_KR(S2DW_WA)
 #undef S2DW_WA
                 break;
@@ -298,7 +301,7 @@ __global__ void __launch_bounds__(kPersistThreads, PART == 0 ? 2 : 3) persist_ke
                                                                   const unsigned char *__restrict__ args, int *ctr,
                                                                   int nctr, PState *state, int *status, int spin_limit,
                                                                   int status_or, int wait_extra, int chunk) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[kPersistLds];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[PART == 1 ? kPersistLds : (DIR == 1 ? kPersistAdjLds : kPersistFwdLds)];
     __shared__ int s_ticket, s_err, s_last;
     const int tid = threadIdx.x;
     // The end of a run of n items of one job and map: every wave waits for its stores, then

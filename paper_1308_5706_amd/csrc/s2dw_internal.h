@@ -20,7 +20,18 @@ constexpr int kMaxSteerAngles = 1 << 16;  // angles per steering call
 struct SegTab {
     int n;
     int s0[kMaxSegs], s1[kMaxSegs];  // [s0, s1)
+    int b0[kMaxSegs];                // first block of the segment in the kappa sigma Delta table
     int8_t je[kMaxSegs], jo[kMaxSegs];  // active even / odd scale, -1 if none
+};
+
+// The same segments as the Wigner kernels read them, one record each and a last one with s1 = 0.
+// Analysis: the band-limit and U offset of the scales of the two parity slots that end with the
+// segment (Le, Lo = 0: none).  Synthesis: the scales active on it (Lae, Lao = 0: none, V offsets),
+// and whether they differ from the segment before.
+struct WigSeg {
+    int s0, s1;
+    int Le, Lo, Lae, Lao, newe, newo;
+    long long offe, offo, offae, offao;
 };
 
 // Per-scale layout of the Wigner-stage workspaces.  Scale j has band-limit Lj (its

@@ -20,12 +20,35 @@ static hipError_t launch_adj_k(const WigAdjArgs &a, int ntiles, int maps, hipStr
     return hipGetLastError();
 }
 
-// m' slots per wave: the accumulators take 16 R K registers, kept at or below 128
-int wig_slots(int K) { return K >= 5 ? 1 : (K >= 2 ? 2 : 4); }
+// m' slots per wave.  The accumulators (analysis) or quadrature values (synthesis) take 16 R K
+// registers, kept at or below 128 for two waves per SIMD.  More slots share the per-lane loads
+// and, in the synthesis, the window sums and the partial sums of a group; but below a few waves
+// per SIMD (1024 of them) a wave's own chain of steps is what takes the time, and fewer slots
+// make it shorter.  Measured (us, one map, FP64; analysis / synthesis with the final sum), slots
+// 1, 2, 4: L = 256, N = 8 (1024 waves at one slot) 43, 61 / 88, 114; L = 421, N = 6 (2947) 59, 77 /
+// 123, 153; L = 512, N = 4 (4096) 87, 76, 122 / 133, 147, 217; L = 512, N = 1 72, 60, 85 / 122, 125,
+// 167; L = 1024, N = 8 (16384) 648, 390 / 804, 582; L = 1024, N = 3 500, 226, 213 / 664, 432, 409;
+// L = 2048, N = 4 3283, 1594, 1454 / 4740, 3131, 2426.
+static int wig_slots(int K, long waves, long one) {
+    const int most = K >= 5 ? 1 : (K >= 3 ? 2 : 4);
+    if (waves <= one) return 1;
+    return waves <= 12000 && most > 2 ? 2 : most;
+}
+int wig_fwd_slots_for(int K, long waves) { return wig_slots(K, waves, 3500); }
+// Mixed precision: one number of slots at every size, so that its FP32 sums over the m' of a group
+// are rounded the same way in every call.
+int wig_adj_slots(int K, long waves, int f32) {
+    if (f32) return K >= 5 ? 1 : (K >= 2 ? 2 : 4);
+    return wig_slots(K, waves, 5000);
+}
 
 // Slot counts compiled for each number of carried orders K (the tile shapes the tuner may pick).
 int wig_slot_options(int K, int *R) {
     if (K <= 1) {
+        R[0] = 1, R[1] = 2, R[2] = 4;
+        return 3;
+    }
+    if (K == 2) {
         R[0] = 1, R[1] = 2, R[2] = 4;
         return 3;
     }
@@ -44,6 +67,7 @@ int wig_slot_options(int K, int *R) {
         case 1 * 8 + 4: return FN<1, 4>(a, ntiles, maps, st);        \
         case 2 * 8 + 1: return FN<2, 1>(a, ntiles, maps, st);        \
         case 2 * 8 + 2: return FN<2, 2>(a, ntiles, maps, st);        \
+        case 2 * 8 + 4: return FN<2, 4>(a, ntiles, maps, st);        \
         case 3 * 8 + 1: return FN<3, 1>(a, ntiles, maps, st);        \
         case 3 * 8 + 2: return FN<3, 2>(a, ntiles, maps, st);        \
         case 4 * 8 + 1: return FN<4, 1>(a, ntiles, maps, st);        \
