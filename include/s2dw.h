@@ -321,15 +321,17 @@ int s2dw_wavelet_tables(const s2dw_params *p, double *kappa, double *phi, double
  * s2dw_profile(0) disables.  s2dw_profile_read waits for the recorded events and
  * fills up to max entries (host memory) with per-stage totals since the last clear;
  * *n receives the number of stages.  Names: pad, wigner_fwd, beta_fwd, alpha_fwd,
- * gamma_fwd, alpha_gamma_fwd (analysis; the last is the fused alpha and gamma pass that
- * the coarse scales of real signals take), gamma_adj, gamma_alpha_adj (its synthesis
- * counterpart, FP64), alpha_adj, beta_adj, wigner_adj, syn_final (synthesis), scaling,
- * steer.
+ * gamma_fwd, alpha_gamma_fwd (analysis; the last is the fused alpha and gamma pass of
+ * real signals), gamma_adj, gamma_alpha_adj (its synthesis counterpart), alpha_adj,
+ * beta_adj, wigner_adj, syn_final (synthesis), scaling, steer.  A launch that takes
+ * several scales counts one pass for each of them.  While stages are timed, the alpha and
+ * gamma sums of scales on grids of band-limit below 64 run as separate passes (with the
+ * same results), so that each has a time.
  */
 typedef struct s2dw_stage_time {
     char name[24];
     double ms;      /* summed device time */
-    int64_t count;  /* launches */
+    int64_t count;  /* passes (launches, times the scales each takes) */
 } s2dw_stage_time;
 int s2dw_profile(int enable);
 int s2dw_profile_read(s2dw_stage_time *out, int32_t max, int32_t *n);

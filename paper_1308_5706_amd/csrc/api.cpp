@@ -88,6 +88,12 @@ struct Plan {
     BetaAdjScale *atab = nullptr;
     size_t goff[kMaxScales] = {};
     BetaAdjScale *mtab = nullptr, *mtabf = nullptr;
+    // every scale's Ub (G) side by side, scale j's at uboff[j], s_Ubs elements per map (0: this
+    // grid's scales share nothing; see side_by_side), and the synthesis beta stage of all of
+    // them on the equiangular grid (stab / stabf, sns scales, snwg workgroups per map)
+    size_t uboff[kMaxScales] = {}, s_Ubs = 0;
+    int sns = 0, snwg = 0;
+    BetaAdjScale *stab = nullptr, *stabf = nullptr;
     size_t woff[kMaxScales + 1] = {};           // element offset of scale j in the W of one map
     // chirp tables of one grid band-limit (length T = 2Lg - 1) and the spectrum of the first
     // synthesis beta convolution (transform size PD)
@@ -150,6 +156,7 @@ struct Work {
     int cap = 0;
     size_t s_F = 0;
     double2 *fpad = nullptr, *U = nullptr, *Ub = nullptr, *Y = nullptr, *Fpart = nullptr;
+    size_t n_Ub = 0;  // elements of Ub
     std::vector<void *> allocs;
     size_t bytes = 0;
     ~Work() {
@@ -170,6 +177,7 @@ struct Prof {
     size_t used = 0;
     struct Rec {
         const char *name;
+        int passes;
         hipEvent_t a, b;
     };
     std::vector<Rec> recs;
@@ -194,12 +202,14 @@ thread_local bool t_no_events = false;
 thread_local Recorder *t_rec = nullptr;  // work-list recording (persistent executor), kernels.h
 namespace {
 
-// Records events around one launch when timing is on.
+// Records events around one launch when timing is on; passes: the stage's passes that the
+// launch makes (one per scale it takes).
 struct Stage {
     hipStream_t st;
     hipEvent_t a = nullptr;
     const char *name;
-    Stage(const char *n, hipStream_t s) : st(s), name(n) {
+    int passes;
+    Stage(const char *n, hipStream_t s, int k = 1) : st(s), name(n), passes(k) {
         if (!g_prof.on || t_no_events) return;
         std::lock_guard<std::mutex> lk(g_prof.mu);
         if (!g_prof.only.empty() && !g_prof.only.count(n)) return;
@@ -212,7 +222,7 @@ struct Stage {
         hipEvent_t b = prof_event();
         if (!b) return;
         hipEventRecord(b, st);
-        g_prof.recs.push_back({name, a, b});
+        g_prof.recs.push_back({name, passes, a, b});
     }
 };
 
@@ -223,7 +233,7 @@ void prof_collect() {
         if (hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
             auto &t = g_prof.totals[r.name];
             t.first += ms;
-            t.second += 1;
+            t.second += r.passes;
         }
     }
     g_prof.recs.clear();
@@ -425,6 +435,13 @@ Shape shape_of(Plan &P) {
     std::lock_guard<std::mutex> lk(g_mu);
     return P.cur;
 }
+
+// The Ub arrays of all scales go side by side, and the scales through each stage together, where
+// those arrays take no more than this.  Measured, ms, together against scale by scale: round
+// trip L = 640, N = 4 (126 MB) 1.10 against 1.38, 32 maps of L = 128, N = 8, mixed (200 MB) 1.00
+// against 1.15, L = 900, N = 8 (311 MB) 3.55 against 3.82, L = 1500, N = 8 (864 MB) 14.15 against
+// 14.36: beyond it a scale fills the chip by itself and the memory is not worth it.
+constexpr size_t kSideBytes = (size_t)512 << 20;
 
 // Default maps per batched launch sequence: as many as fit 8 GiB of workspace, at most 64.
 int default_chunk(const Plan &P) {
@@ -829,6 +846,19 @@ int build_plan(int kind, int L, int N, double lam, int J_min, int grid, Plan *&o
         if (!upload(P, P.hA[j], ha) || !upload(P, P.hB[j], hb) || !upload(P, P.hC[j], hc) || !upload(P, P.hD2[j], hd2))
             return S2DW_E_NOMEM;
     }
+    if (grid != S2DW_GRID_MW_MULTIRES && kind == kWavelet && !pfa_length(2 * L - 1)) {
+        std::vector<BetaAdjScale> tab;
+        for (int j = 0; j < t.S; ++j) {
+            const int Lj = P.sc.Lj[j];
+            if (Lj == 0) continue;
+            P.uboff[j] = P.s_Ubs;
+            P.s_Ubs += (size_t)t.N * Lj * P.nb;
+            tab.push_back(BetaAdjScale{P.snwg, Lj, (long long)P.uboff[j], (long long)P.sc.off[j], (const void *)P.hD2[j]});
+            P.snwg += P.K * ((Lj + 1) / 2);
+        }
+        P.sns = (int)tab.size();
+        if (!dh && !tab.empty() && !upload(P, P.stab, tab)) return S2DW_E_NOMEM;
+    }
     if (grid == S2DW_GRID_MW && kind == kWavelet) {
         // coarse scales (at most 256 order-column pairs each) at the end of the scale list, as many
         // as the beta-stage workspace holds side by side (sum of their Lj <= the largest Lj)
@@ -939,6 +969,13 @@ int ensure_f32(Plan &P) {
             if (P.sc.Lj[j] > 0) tab[i++].hh2 = P.hD2f[j];
         ok = ok && upload(P, P.mtabf, tab);
     }
+    if (ok && P.stab) {
+        std::vector<BetaAdjScale> tab(P.sns);
+        ok = hipMemcpy(tab.data(), P.stab, sizeof(BetaAdjScale) * P.sns, hipMemcpyDeviceToHost) == hipSuccess;
+        for (int i = 0, j = 0; ok && j < P.S; ++j)
+            if (P.sc.Lj[j] > 0) tab[i++].hh2 = P.hD2f[j];
+        ok = ok && upload(P, P.stabf, tab);
+    }
     for (auto &kv : P.twP) {
         if (!ok) break;
         float2 *d = nullptr;
@@ -989,6 +1026,16 @@ bool walloc(Work &w, T *&p, size_t count) {
     return true;
 }
 
+// Maps whose Ub arrays of every scale go side by side: as many as fit kSideBytes.
+int side_maps(const Plan &P) {
+    return P.s_Ubs ? (int)std::min<size_t>(kSideBytes / (P.s_Ubs * sizeof(double2)), 1024) : 0;
+}
+
+// Elements of the beta-stage workspace for `maps` maps.
+size_t ub_elements(const Plan &P, int maps) {
+    return std::max((size_t)maps * P.s_Ub, (size_t)std::min(maps, side_maps(P)) * P.s_Ubs);
+}
+
 // The workspace of `stream` for a batch of `maps` maps with per-map partial sums of s_F
 // elements (grown on demand: the first call on a stream, a larger batch or a larger
 // partial-sum layout allocates; the old buffers are freed after that stream drains, and only
@@ -1007,7 +1054,8 @@ int get_work(Plan &P, hipStream_t stream, int maps, size_t s_F, Work *&out) {
     std::unique_ptr<Work> w(new (std::nothrow) Work());
     if (!w) return S2DW_E_NOMEM;
     const size_t n = (size_t)maps;
-    if (!walloc(*w, w->fpad, n * P.s_fpad) || !walloc(*w, w->U, n * P.s_U) || !walloc(*w, w->Ub, n * P.s_Ub) ||
+    w->n_Ub = ub_elements(P, maps);
+    if (!walloc(*w, w->fpad, n * P.s_fpad) || !walloc(*w, w->U, n * P.s_U) || !walloc(*w, w->Ub, w->n_Ub) ||
         !walloc(*w, w->Y, n * P.s_Y) || !walloc(*w, w->Fpart, n * s_F))
         return S2DW_E_NOMEM;
     w->cap = maps;
@@ -1077,6 +1125,38 @@ bool fuse_adj(const Plan &P, const Shape &sh, int f32, int T) {
     return T == 4095 || f32 || P.Nh <= 2;
 }
 
+// Whether scale j takes the fused alpha and gamma kernel with chirp convolutions (fused_k.h).
+// FP64 also in place of the blocked transforms (analysis L = 512, N = 4 on the Driscoll-Healy grid,
+// scale by scale: 0.499 ms against 0.526); the mixed path keeps those, whose FP32 rounding is part
+// of its results.
+bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
+    if (t_rec || cx || !fused_fft(P.PB[j], P.Nh) || pfa_length(2 * P.Lg[j] - 1)) return false;
+    // while stages are timed, the alpha and gamma sums of the smallest maps (in no size blocked, so
+    // with the same results) stay apart, each with a time of its own
+    if (g_prof.on && !t_no_events && P.Lg[j] < 64) return false;
+    return P.nblkb[j] <= 1 || !f32;
+}
+
+// Whether the scales of this call go through each stage together (kSideBytes): as separate
+// launches per scale, the calls up to L of a few hundred spend more time between launches and in
+// their last waves than in full ones (analysis L = 64, N = 3: 21 launches, 113 us, against 8 and
+// 48 us).  The call that allocates nothing and the persistent program keep a scale's room.
+bool side_by_side(const Plan &P, const Work &w, int maps, bool cx) {
+    return !t_rec && !cx && P.s_Ubs > 0 && maps <= side_maps(P) && (size_t)maps * P.s_Ubs <= w.n_Ub;
+}
+
+// Scales that share a launch: same kernel (kind) and transform size.
+struct RefGroup {
+    int kind, size, nwg;
+    ScaleRefs refs;
+};
+void add_ref(std::vector<RefGroup> &v, int kind, int size, int nwg, int Lj, size_t in_off, size_t out_off, const void *hh) {
+    if (v.empty() || v.back().kind != kind || v.back().size != size) v.push_back(RefGroup{kind, size, 0, {}});
+    RefGroup &g = v.back();
+    g.refs.s[g.refs.n++] = ScaleRef{g.nwg, Lj, (long long)in_off, (long long)out_off, hh};
+    g.nwg += nwg;
+}
+
 // Coarse scales of real signals take the fused alpha and gamma passes (the analysis one
 // in both precisions: it computes in FP64 and reads and writes Ub and W in the plan's
 // precision; the synthesis one in FP64) while Nh (2Lj - 1) stays within 9 G and 256 (the
@@ -1135,6 +1215,46 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     const size_t per_map = P.woff[P.S];  // elements of one W (complex ones with cx)
     const size_t ew = (f32 ? 4 : 8) * (cx ? 2 : 1);
     const int wmaps = cx ? maps / 2 : maps;
+    const bool side = side_by_side(P, w, maps, cx);
+    const size_t s_Ub = side ? P.s_Ubs : P.s_Ub;
+    std::vector<RefGroup> direct, fused;  // scales whose alpha and gamma sums follow the loop
+    StageArgs sb{};                       // the arguments all scales share (side by side)
+    if (side) {
+        const bool dh = P.grid == S2DW_GRID_DH;
+        const Plan::GridTab &gtab = P.gt[L];
+        std::vector<RefGroup> beta;
+        for (int j = 0; j < P.S; ++j) {
+            const int Lj = P.sc.Lj[j];
+            if (Lj == 0) continue;
+            const bool pair = !dh && pow2_at_least(2 * Lj + 2 * L - 3) <= P.PA[j];
+            add_ref(beta, pair ? 1 : 0, P.PA[j], N * (pair ? (Lj + 1) / 2 : Lj), Lj, P.sc.off[j], P.uboff[j],
+                    f32 ? (const void *)P.hAf[j] : P.hA[j]);
+        }
+        sb.f32 = f32;
+        sb.in = w.U;
+        sb.out = w.Ub;
+        sb.s_in = P.s_U;
+        sb.s_out = s_Ub;
+        sb.csq = dh ? (f32 ? (const void *)P.dh_csqf : P.dh_csq) : (f32 ? (const void *)gtab.csqf : gtab.csq);
+        sb.cpp = dh ? (f32 ? (const void *)P.dh_cppf : P.dh_cpp) : (f32 ? (const void *)gtab.cppf : gtab.cpp);
+        sb.L = L;
+        sb.nb = P.nb;
+        sb.N = N;
+        sb.Nh = P.Nh;
+        for (const RefGroup &g : beta) {
+            sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
+            Stage sg("beta_fwd", st, g.refs.n);
+            S2DW_CHECK_HIP(g.kind ? launch_beta_fwd_pair(sb, g.size, maps, st, &g.refs, g.nwg)
+                                  : launch_beta_fwd_fft(sb, g.size, maps, st, &g.refs, g.nwg));
+        }
+        sb.in = w.Ub;
+        sb.s_in = s_Ub;
+        sb.wout = W;
+        sb.s_w = per_map;
+        sb.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
+        sb.tg = f32 ? (const void *)P.tgff : P.tgf;
+        sb.G = P.ng;
+    }
     for (int j = 0; j < P.S; ++j) {
         const int Lj = P.sc.Lj[j], Lg = P.Lg[j];
         const size_t per_scale = P.woff[j + 1] - P.woff[j];
@@ -1148,13 +1268,14 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
         // coarse scales: the beta stage of all of them in one launch at the first, each scale's
         // Ub at goff[j]
         const bool bmerged = P.ans > 0 && j >= P.mj0 && gtab.pcs && P.grid == S2DW_GRID_MW;
-        void *ubj = bmerged ? (f32 ? (void *)((float2 *)w.Ub + P.goff[j]) : (void *)(w.Ub + P.goff[j])) : (void *)w.Ub;
+        const size_t uo = side ? P.uboff[j] : (bmerged ? P.goff[j] : 0);
+        void *ubj = f32 ? (void *)((float2 *)w.Ub + uo) : (void *)(w.Ub + uo);
         StageArgs b{};
         b.f32 = f32;
         b.in = w.U + P.sc.off[j];
         b.out = w.Ub;
         b.s_in = P.s_U;
-        b.s_out = P.s_Ub;
+        b.s_out = s_Ub;
         b.hh = f32 ? (const void *)P.hAf[j] : P.hA[j];
         b.tw = f32 ? (const void *)P.twPf[P.PA[j]] : P.twP[P.PA[j]];
         const bool dh = P.grid == S2DW_GRID_DH;
@@ -1165,7 +1286,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
         b.Lj = Lj;
         b.N = N;
         b.Nh = P.Nh;
-        {
+        if (!side) {
             Stage sg("beta_fwd", st);
             // two columns per transform: as a prime-factor transform of length T where T is one
             // of its lengths, else as a chirp convolution where that needs no larger transform
@@ -1188,12 +1309,16 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
                 S2DW_CHECK_HIP(launch_beta_fwd_fft(b, P.PA[j], maps, st));
         }
         if (direct_alpha_gamma(P.Nh, P.ng, Lj, cx)) {
+            if (side) {
+                add_ref(direct, 0, 0, 0, Lj, P.uboff[j], P.woff[j], nullptr);
+                continue;
+            }
             AlphaGammaArgs d{};
             d.in = ubj;
             d.wout = Wj;
             d.tg = P.tgf;
             d.eph = gtab.eph;
-            d.s_in = P.s_Ub;
+            d.s_in = s_Ub;
             d.s_w = per_map;
             d.nb = b.nb;
             d.T = 2 * Lg - 1;
@@ -1210,7 +1335,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             // the alpha and gamma passes in one prime-factor kernel, one beta ring per workgroup
             StageArgs d = b;
             d.in = ubj;
-            d.s_in = P.s_Ub;
+            d.s_in = s_Ub;
             d.pcs = f32 ? (const void *)gtab.pcsf : gtab.pcs;
             d.wout = Wj;
             d.s_w = per_map;
@@ -1220,10 +1345,30 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             S2DW_CHECK_HIP(launch_alpha_gamma_fwd_pfa(d, maps, st));
             continue;
         }
+        if (fuse_fft(P, f32, j, cx)) {
+            const int nwg = 8 * ((b.nb + 7) / 8);
+            const void *hh = f32 ? (const void *)P.hBf[j] : P.hB[j];
+            if (side) {
+                add_ref(fused, 0, P.PB[j], nwg, Lj, P.uboff[j], P.woff[j], hh);
+                continue;
+            }
+            StageArgs d = b;
+            d.in = ubj;
+            d.s_in = s_Ub;
+            d.wout = Wj;
+            d.s_w = per_map;
+            d.tg = f32 ? (const void *)P.tgff : P.tgf;
+            d.G = P.ng;
+            d.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
+            d.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
+            Stage sg("alpha_gamma_fwd", st);
+            S2DW_CHECK_HIP(launch_alpha_gamma_fwd_fft(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, st));
+            continue;
+        }
         StageArgs c = b;
         c.in = ubj;
         c.out = w.Y;
-        c.s_in = P.s_Ub;
+        c.s_in = s_Ub;
         c.s_out = P.s_Y;
         c.hh = f32 ? (const void *)P.hBf[j] : P.hB[j];
         c.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
@@ -1262,6 +1407,29 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             else S2DW_CHECK_HIP(launch_gamma_fwd(g, maps, st));
         }
     }
+    for (const RefGroup &g : fused) {
+        sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
+        Stage sg("alpha_gamma_fwd", st, g.refs.n);
+        S2DW_CHECK_HIP(launch_alpha_gamma_fwd_fft(sb, g.refs, g.nwg, g.size, maps, st));
+    }
+    for (const RefGroup &g : direct) {
+        AlphaGammaArgs d{};
+        d.in = w.Ub;
+        d.wout = W;
+        d.tg = P.tgf;
+        d.eph = P.gt[L].eph;
+        d.s_in = s_Ub;
+        d.s_w = per_map;
+        d.nb = P.nb;
+        d.T = 2 * L - 1;
+        for (int i = 0; i < g.refs.n; ++i) d.Lj = std::max(d.Lj, g.refs.s[i].Lj);
+        d.N = N;
+        d.Nh = P.Nh;
+        d.G = P.ng;
+        d.f32 = f32;
+        Stage sg("alpha_gamma_fwd", st, g.refs.n);
+        S2DW_CHECK_HIP(launch_alpha_gamma_fwd(d, maps, st, &g.refs));
+    }
     return S2DW_OK;
 }
 
@@ -1274,6 +1442,11 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
     const int L = P.L, N = P.ht.N;
     const size_t per_map = P.woff[P.S];
     const size_t ew = (f32 ? 4 : 8) * (cx ? 2 : 1);
+    const bool side = side_by_side(P, w, maps, cx);
+    const size_t s_Ub = side ? P.s_Ubs : P.s_Ub;
+    StageArgs sb{};
+    GammaAlphaArgs sd{};
+    std::vector<RefGroup> direct, fusedg, betadh;  // scales whose sums follow the loop
     for (int j = 0; j < P.S; ++j) {
         const int Lj = P.sc.Lj[j], Lg = P.Lg[j], M = 2 * Lg - 1;
         if (Lj == 0) continue;
@@ -1291,15 +1464,41 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
         g.G = P.ng;
         g.Nh = P.Nh;
         g.f32 = f32;
-        const bool merged = P.mj0 >= 0 && j >= P.mj0;  // synthesis beta stage in the coarse-scale launch
-        void *gout = !merged ? (void *)w.Ub
-                             : (f32 ? (void *)((float2 *)w.Ub + P.goff[j]) : (void *)(w.Ub + P.goff[j]));
+        const bool merged = side || (P.mj0 >= 0 && j >= P.mj0);  // synthesis beta stage in the coarse-scale launch
+        const size_t uo = side ? P.uboff[j] : (merged ? P.goff[j] : 0);
+        void *gout = f32 ? (void *)((float2 *)w.Ub + uo) : (void *)(w.Ub + uo);
         const double qscale = (2.0 * M_PI / M) * (2.0 * M_PI / P.ng);  // alpha and gamma quadrature weights
         // FP64 only: the fused pass computes in FP64 and is bound by its arithmetic at the
         // larger Lj, where the FP32 passes of the mixed path are cheaper
         const bool fused = direct_alpha_gamma(P.Nh, P.ng, Lj, cx) && !f32;
         const bool fused_pfa = !fused && gtab.pcs && !cx && pfa_fused(M, P.Nh) && fuse_adj(P, sh, f32, M);
-        if (fused_pfa) {
+        const bool fused_ch = !fused && fuse_fft(P, f32, j, cx);
+        if (fused_ch) {
+            const int nwg = 8 * ((g.L + 7) / 8);
+            const void *hh = f32 ? (const void *)P.hCf[j] : P.hC[j];
+            StageArgs d{};
+            d.f32 = f32;
+            d.win = side ? W : Wj;
+            d.s_w = per_map;
+            d.tg = f32 ? (const void *)P.tgaf : P.tga;
+            d.G = P.ng;
+            d.out = side ? (void *)w.Ub : gout;
+            d.s_out = s_Ub;
+            d.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
+            d.L = Lg;
+            d.nb = g.L;
+            d.N = N;
+            d.Nh = P.Nh;
+            d.scale = qscale;
+            d.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
+            if (side) {
+                add_ref(fusedg, 0, P.PB[j], nwg, Lj, P.woff[j], uo, hh);
+                sb = d;
+            } else {
+                Stage sg("gamma_alpha_adj", st);
+                S2DW_CHECK_HIP(launch_gamma_alpha_adj_fft(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, st));
+            }
+        } else if (fused_pfa) {
             StageArgs d{};
             d.f32 = f32;
             d.win = Wj;
@@ -1307,7 +1506,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             d.tg = f32 ? (const void *)P.tgaf : P.tga;
             d.G = P.ng;
             d.out = gout;
-            d.s_out = P.s_Ub;
+            d.s_out = s_Ub;
             d.pcs = f32 ? (const void *)gtab.pcsf : gtab.pcs;
             d.L = Lg;
             d.nb = g.L;
@@ -1319,12 +1518,12 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             S2DW_CHECK_HIP(launch_gamma_alpha_adj_pfa(d, maps, st));
         } else if (fused) {
             GammaAlphaArgs d{};
-            d.win = Wj;
-            d.out = gout;
+            d.win = side ? W : Wj;
+            d.out = side ? (void *)w.Ub : gout;
             d.tg = P.tga;
             d.eph = gtab.eph;
             d.s_w = per_map;
-            d.s_out = P.s_Ub;
+            d.s_out = s_Ub;
             d.nb = g.L;
             d.T = M;
             d.Lj = Lj;
@@ -1333,8 +1532,14 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             d.G = P.ng;
             d.scale = qscale;
             d.f32 = f32;
-            Stage sg("gamma_alpha_adj", st);
-            S2DW_CHECK_HIP(launch_gamma_alpha_adj(d, maps, st));
+            if (side) {
+                add_ref(direct, 0, 0, 0, Lj, P.woff[j], uo, nullptr);
+                d.Lj = std::max(d.Lj, sd.Lj);
+                sd = d;
+            } else {
+                Stage sg("gamma_alpha_adj", st);
+                S2DW_CHECK_HIP(launch_gamma_alpha_adj(d, maps, st));
+            }
         } else {
             Stage sg("gamma_adj", st);
             if (cx) S2DW_CHECK_HIP(launch_gamma_adj_cx(g, maps / 2, st));
@@ -1345,7 +1550,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
         c.in = w.Y;
         c.out = gout;
         c.s_in = P.s_Y;
-        c.s_out = P.s_Ub;
+        c.s_out = s_Ub;
         c.hh = f32 ? (const void *)P.hCf[j] : P.hC[j];
         c.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
         c.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
@@ -1357,7 +1562,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
         c.Nh = P.Nh;
         c.K = P.K;
         c.scale = qscale;
-        if (fused || fused_pfa) {
+        if (fused || fused_pfa || fused_ch) {
             // the alpha quadrature ran in the fused pass above
         } else if (P.nblkb[j] <= 1 && gtab.pcs) {
             StageArgs cp = c;
@@ -1377,6 +1582,8 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             Stage sg("alpha_adj", st);
             S2DW_CHECK_HIP(launch_alpha_adj_fft(c, P.PB[j], maps, st));
         }
+        if (side && dh)
+            add_ref(betadh, 0, P.PE[j], P.K * Lj, Lj, uo, P.sc.off[j], f32 ? (const void *)P.hEf[j] : P.hE[j]);
         if (merged) continue;
         StageArgs v = c;
         v.in = w.Ub;
@@ -1405,29 +1612,48 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             S2DW_CHECK_HIP(launch_beta_adj_fft(v, gtab.PD, maps, st));
         }
     }
-    if (P.mj0 >= 0) {
+    for (const RefGroup &g : fusedg) {
+        sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
+        Stage sg("gamma_alpha_adj", st, g.refs.n);
+        S2DW_CHECK_HIP(launch_gamma_alpha_adj_fft(sb, g.refs, g.nwg, g.size, maps, st));
+    }
+    for (const RefGroup &g : direct) {
+        Stage sg("gamma_alpha_adj", st, g.refs.n);
+        S2DW_CHECK_HIP(launch_gamma_alpha_adj(sd, maps, st, &g.refs));
+    }
+    if (!betadh.empty() || (side && P.sns > 0) || P.mj0 >= 0) {
+        const bool dh = P.grid == S2DW_GRID_DH;
         const Plan::GridTab &gtab = P.gt[L];
         StageArgs v{};
         v.f32 = f32;
         v.in = w.Ub;
         v.out = w.U;
-        v.s_in = P.s_Ub;
+        v.s_in = s_Ub;
         v.s_out = P.s_U;
-        v.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
-        v.cpp = f32 ? (const void *)gtab.cppf : gtab.cpp;
+        v.csq = dh ? (f32 ? (const void *)P.dh_csqf : P.dh_csq) : (f32 ? (const void *)gtab.csqf : gtab.csq);
+        v.cpp = dh ? (f32 ? (const void *)P.dh_cppf : P.dh_cpp) : (f32 ? (const void *)gtab.cppf : gtab.cpp);
+        v.qw = f32 ? (const void *)P.dh_qf : P.dh_q;
         v.hh = f32 ? (const void *)gtab.hD1f : gtab.hD1;
         v.tw = f32 ? (const void *)P.twPf[gtab.PD] : P.twP[gtab.PD];
         v.eph = f32 ? (const void *)gtab.ephf : gtab.eph;
         v.pcs = f32 ? (const void *)gtab.pcsf : gtab.pcs;
         v.L = L;
-        v.nb = L;
+        v.nb = P.nb;
         v.N = N;
         v.Nh = P.Nh;
         v.K = P.K;
         for (int k = 0; k < P.K; ++k) v.nk[k] = P.ht.nk[k];
         v.eta_imag = P.ht.eta_imag ? 1 : 0;
-        Stage sg("beta_adj", st);
-        S2DW_CHECK_HIP(launch_beta_adj_multi(v, f32 ? P.mtabf : P.mtab, P.mns, P.mnwg, gtab.PD, maps, st));
+        for (const RefGroup &g : betadh) {
+            v.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
+            Stage sg("beta_adj", st, g.refs.n);
+            S2DW_CHECK_HIP(launch_beta_adj_dh(v, g.size, maps, st, &g.refs, g.nwg));
+        }
+        if (!dh) {
+            Stage sg("beta_adj", st, side ? P.sns : 1);
+            if (side) S2DW_CHECK_HIP(launch_beta_adj_multi(v, f32 ? P.stabf : P.stab, P.sns, P.snwg, gtab.PD, maps, st));
+            else S2DW_CHECK_HIP(launch_beta_adj_multi(v, f32 ? P.mtabf : P.mtab, P.mns, P.mnwg, gtab.PD, maps, st));
+        }
     }
     WigAdjArgs a{};
     a.pq = P.pq;
@@ -2099,9 +2325,10 @@ int s2dw_workspace_bytes(const s2dw_params *p, int32_t count, uint64_t *bytes) {
     rc = get_plan(kWavelet, p->L, p->N, p->lambda, p->J_min, P, p->precision == S2DW_MIXED, p->grid);
     if (rc != S2DW_OK) return rc;
     const Shape sh = shape_of(*P);
-    const uint64_t per_map = 16ull * (P->s_fpad + P->s_U + P->s_Ub + P->s_Y + sh.s_F());
+    const uint64_t per_map = 16ull * (P->s_fpad + P->s_U + P->s_Y + sh.s_F());
     const int per = p->reality == 0 ? 2 : 1;  // real maps per signal
-    *bytes = per_map * per * (uint64_t)std::min<int>(count, std::max(sh.chunk / per, 1));
+    const int maps = per * std::min<int>(count, std::max(sh.chunk / per, 1));
+    *bytes = per_map * maps + 16ull * ub_elements(*P, maps);
     return S2DW_OK;
 }
 

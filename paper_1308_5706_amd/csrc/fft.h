@@ -307,8 +307,8 @@ __device__ __forceinline__ void mid_pass(int tid0, const C *__restrict__ tw, con
 // Forward passes: radix RM (span 1, RM, ...), then the partial radix last; inverse passes:
 // the partial radix first, then radix RM.  The pass at the junction is fused (mid_pass).
 // n_in: `in` returns zero at every index >= n_in (with RM = 8 and n_in <= P/2 the first
-// pass skips the zero half).
-template <int P, int RM, class C, class In, class Out>
+// pass skips the zero half; LOW = 1 or 0 where that is known at compile time).
+template <int P, int RM, int LOW = -1, class C, class In, class Out>
 __device__ __forceinline__ void convolve_io(C *buf, int tid, const C *__restrict__ tw, const C *__restrict__ hh,
                                             In in, Out out, int n_in = P) {
     static_assert(P >= 32 && (P & (P - 1)) == 0, "power of two >= 32");
@@ -323,7 +323,9 @@ __device__ __forceinline__ void convolve_io(C *buf, int tid, const C *__restrict
     for (int s = 0; s < NSIDE; ++s) {
         if (s == 0) {
             if constexpr (RM == 8) {
-                if (n_in <= P / 2) pass_first_low<P, NT, -1, C>(tid, in, lo);
+                if constexpr (LOW == 1) pass_first_low<P, NT, -1, C>(tid, in, lo);
+                else if constexpr (LOW == 0) pass<P, NT, RM, -1>(Ns, tid, tw, in, lo);
+                else if (n_in <= P / 2) pass_first_low<P, NT, -1, C>(tid, in, lo);
                 else pass<P, NT, RM, -1>(Ns, tid, tw, in, lo);
             } else {
                 pass<P, NT, RM, -1>(Ns, tid, tw, in, lo);

@@ -97,10 +97,31 @@ struct StageArgs {
     int nk[kMaxK];
     double scale;
 };
-// Every launcher takes the number of maps of the batch (grid y).
-hipError_t launch_beta_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t st);
+// The scales of one launch (same grid, same transform size): the first workgroup of each, its
+// band-limit, the element offsets of its input and output from the launch's in and out (W: from
+// win, wout, in real elements), and its spectrum.
+struct ScaleRef {
+    int first, Lj;
+    long long in_off, out_off;
+    const void *hh;
+};
+struct ScaleRefs {
+    int n;
+    ScaleRef s[kMaxScales];
+};
+// Every launcher takes the number of maps of the batch (grid y).  With refs (nwg workgroups per
+// map in all), the launch takes several scales; without, the one that a describes.
+hipError_t launch_beta_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t st, const ScaleRefs *refs = nullptr,
+                               int nwg = 0);
 // Equiangular grid only: columns (n, m) and (n, m + 1) in one transform of size P >= 2Lj + 2L - 3.
-hipError_t launch_beta_fwd_pair(const StageArgs &a, int P, int maps, hipStream_t st);
+hipError_t launch_beta_fwd_pair(const StageArgs &a, int P, int maps, hipStream_t st, const ScaleRefs *refs = nullptr,
+                                int nwg = 0);
+// The alpha and gamma passes of one or more scales in one kernel with chirp convolutions of size P
+// (real signals, Nh <= 4, P >= 128): analysis Ub -> W, synthesis W -> G (scaled by a.scale);
+// 8 ceil(nb / 8) workgroups per scale (fused_k.h).
+bool fused_fft(int P, int Nh);
+hipError_t launch_alpha_gamma_fwd_fft(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, hipStream_t st);
+hipError_t launch_gamma_alpha_adj_fft(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_adj_fft(const StageArgs &a, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_fwd_blk(const StageArgs &a, int P, int maps, hipStream_t st);
@@ -119,7 +140,8 @@ hipError_t launch_alpha_gamma_fwd_pfa(const StageArgs &a, int maps, hipStream_t 
 hipError_t launch_gamma_alpha_adj_pfa(const StageArgs &a, int maps, hipStream_t st);
 hipError_t launch_alpha_adj_blk(const StageArgs &a, int P, int maps, hipStream_t st);
 hipError_t launch_beta_adj_fft(const StageArgs &a, int P, int maps, hipStream_t st);
-hipError_t launch_beta_adj_dh(const StageArgs &a, int P, int maps, hipStream_t st);
+hipError_t launch_beta_adj_dh(const StageArgs &a, int P, int maps, hipStream_t st, const ScaleRefs *refs = nullptr,
+                              int nwg = 0);
 // One scale of a multi-scale beta launch: its first workgroup, band-limit, the offsets
 // (elements) of its input and output in the stage arrays (synthesis: G and V; analysis: U and
 // Ub), and, in the synthesis, its w(q) spectrum.
@@ -158,7 +180,8 @@ struct AlphaGammaArgs {
     size_t s_in, s_w;
     int nb, T, Lj, N, Nh, G, f32;
 };
-hipError_t launch_alpha_gamma_fwd(const AlphaGammaArgs &a, int maps, hipStream_t st);
+// With refs: every scale of it in one launch (in_off into in, out_off into wout).
+hipError_t launch_alpha_gamma_fwd(const AlphaGammaArgs &a, int maps, hipStream_t st, const ScaleRefs *refs = nullptr);
 // Synthesis gamma and alpha quadratures of one coarse scale in one pass (real signals): W
 // [G][nb][T] (per-map stride s_w real elements) -> G [N][Lj][nb] (per-map stride s_out
 // complex elements), both FP32 with f32; tg = e^{-i n gamma_g} [G][Nh] and eph =
@@ -173,7 +196,7 @@ struct GammaAlphaArgs {
     int nb, T, Lj, N, Nh, G, f32;
     double scale;
 };
-hipError_t launch_gamma_alpha_adj(const GammaAlphaArgs &a, int maps, hipStream_t st);
+hipError_t launch_gamma_alpha_adj(const GammaAlphaArgs &a, int maps, hipStream_t st, const ScaleRefs *refs = nullptr);
 hipError_t launch_gamma_adj(const GammaArgs &a, int maps, hipStream_t st);
 // Complex signals: complex map z of W (s_w complex elements per map, (re, im) pairs) from /
 // to the real maps 2z and 2z + 1 of Y / X; cmaps complex maps.

@@ -30,15 +30,41 @@ namespace s2dw {
         S2DW_P_SWITCH_T(double2, P, KER, GRID, ARGS)                         \
     }
 
-hipError_t launch_beta_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t st) {
-    if (t_rec) return rec_fft(PS_BETAF_FFT, a, a.f32, P, (long long)a.N * a.Lj, maps);
-    S2DW_P_SWITCH(P, beta_fwd_fft_kernel, a.N * a.Lj, a)
+// The launch's one scale as a table.
+static ScaleRefs one_scale(const StageArgs &a) { return ScaleRefs{1, {{0, a.Lj, 0, 0, a.hh}}}; }
+
+#define S2DW_R_CASE(C, KER, PV) \
+    case PV: hipLaunchKernelGGL((KER<C, PV>), dim3(nwg, maps), dim3(PV / kRM), 0, st, a, r); break;
+
+#define S2DW_R_SWITCH_T(C, KER)                                                              \
+    switch (P) {                                                                             \
+        S2DW_R_CASE(C, KER, 32) S2DW_R_CASE(C, KER, 64) S2DW_R_CASE(C, KER, 128)             \
+        S2DW_R_CASE(C, KER, 256) S2DW_R_CASE(C, KER, 512) S2DW_R_CASE(C, KER, 1024)          \
+        S2DW_R_CASE(C, KER, 2048) S2DW_R_CASE(C, KER, 4096) S2DW_R_CASE(C, KER, 8192)        \
+        default: return hipErrorInvalidValue;                                                \
+    }
+
+#define S2DW_R_SWITCH(KER)                    \
+    if (a.f32) {                              \
+        S2DW_R_SWITCH_T(float2, KER)          \
+    } else {                                  \
+        S2DW_R_SWITCH_T(double2, KER)         \
+    }
+
+hipError_t launch_beta_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t st, const ScaleRefs *refs, int nwg) {
+    if (t_rec) return refs ? hipErrorNotSupported : rec_fft(PS_BETAF_FFT, a, a.f32, P, (long long)a.N * a.Lj, maps);
+    if (!refs) nwg = a.N * a.Lj;
+    const ScaleRefs r = refs ? *refs : one_scale(a);
+    S2DW_R_SWITCH(beta_fwd_fft_kernel)
     return hipGetLastError();
 }
 
-hipError_t launch_beta_fwd_pair(const StageArgs &a, int P, int maps, hipStream_t st) {
-    if (t_rec) return rec_fft(PS_BETAF_PAIR, a, a.f32, P, (long long)a.N * ((a.Lj + 1) / 2), maps);
-    S2DW_P_SWITCH(P, beta_fwd_pair_kernel, a.N * ((a.Lj + 1) / 2), a)
+hipError_t launch_beta_fwd_pair(const StageArgs &a, int P, int maps, hipStream_t st, const ScaleRefs *refs, int nwg) {
+    const int one = a.N * ((a.Lj + 1) / 2);
+    if (t_rec) return refs ? hipErrorNotSupported : rec_fft(PS_BETAF_PAIR, a, a.f32, P, (long long)one, maps);
+    if (!refs) nwg = one;
+    const ScaleRefs r = refs ? *refs : one_scale(a);
+    S2DW_R_SWITCH(beta_fwd_pair_kernel)
     return hipGetLastError();
 }
 
@@ -125,6 +151,8 @@ bool pfa_fused(int T, int Nh) {
     if (T == 4095) return Nh >= 1 && Nh <= 2;  // one order per pass, 8 samples per thread (512)
     return false;
 }
+
+bool fused_fft(int P, int Nh) { return Nh >= 1 && Nh <= 4 && P >= 128 && P <= 8192; }
 
 #define S2DW_FUSED_CASE(KER, LN, NH)                                                                     \
     case NH:                                                                                             \
@@ -215,9 +243,11 @@ hipError_t launch_beta_adj_multi(const StageArgs &a, const BetaAdjScale *tab, in
     return hipGetLastError();
 }
 
-hipError_t launch_beta_adj_dh(const StageArgs &a, int P, int maps, hipStream_t st) {
+hipError_t launch_beta_adj_dh(const StageArgs &a, int P, int maps, hipStream_t st, const ScaleRefs *refs, int nwg) {
     if (t_rec) return hipErrorNotSupported;
-    S2DW_P_SWITCH(P, beta_adj_dh_kernel, a.K * a.Lj, a)
+    if (!refs) nwg = a.K * a.Lj;
+    const ScaleRefs r = refs ? *refs : one_scale(a);
+    S2DW_R_SWITCH(beta_adj_dh_kernel)
     return hipGetLastError();
 }
 
@@ -244,16 +274,19 @@ hipError_t launch_gamma_fwd(const GammaArgs &a, int maps, hipStream_t st) S2DW_G
 
 hipError_t launch_gamma_adj(const GammaArgs &a, int maps, hipStream_t st) S2DW_GAMMA_LAUNCH(gamma_adj_kernel, PS_GAMMAA)
 
-hipError_t launch_gamma_alpha_adj(const GammaAlphaArgs &a, int maps, hipStream_t st) {
+hipError_t launch_gamma_alpha_adj(const GammaAlphaArgs &a, int maps, hipStream_t st, const ScaleRefs *refs) {
     if (a.Nh < 1 || a.Nh > kMaxK || a.Lj < 1 || a.Nh * (2 * a.Lj - 1) > 256 || a.T < 1 || a.nb < 1 || a.G < 1 ||
         a.G > 4 * a.Nh - 1 || maps < 1)
         return hipErrorInvalidValue;
-    if (t_rec) return rec_job(pkind(PS_GAA, a.f32, a.Nh), a.nb, maps, 256, a);
-    const dim3 grid((unsigned)a.nb, (unsigned)maps);
+    if (t_rec) return refs ? hipErrorNotSupported : rec_job(pkind(PS_GAA, a.f32, a.Nh), a.nb, maps, 256, a);
+    const ScaleRefs r = refs ? *refs : ScaleRefs{1, {{0, a.Lj, 0, 0, nullptr}}};
+    for (int i = 0; i < r.n; ++i)
+        if (r.s[i].Lj < 1 || r.s[i].Lj > a.Lj) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)a.nb, (unsigned)(maps * r.n));
     switch (a.Nh * 2 + (a.f32 ? 1 : 0)) {
 #define S2DW_GA_CASE(NH)                                                                                    \
-    case 2 * NH: hipLaunchKernelGGL((gamma_alpha_adj_kernel<NH, double2>), grid, dim3(256), 0, st, a); break; \
-    case 2 * NH + 1: hipLaunchKernelGGL((gamma_alpha_adj_kernel<NH, float2>), grid, dim3(256), 0, st, a); break;
+    case 2 * NH: hipLaunchKernelGGL((gamma_alpha_adj_kernel<NH, double2>), grid, dim3(256), 0, st, a, r); break; \
+    case 2 * NH + 1: hipLaunchKernelGGL((gamma_alpha_adj_kernel<NH, float2>), grid, dim3(256), 0, st, a, r); break;
         S2DW_GA_CASE(1)
         S2DW_GA_CASE(2)
         S2DW_GA_CASE(3)
@@ -268,21 +301,25 @@ hipError_t launch_gamma_alpha_adj(const GammaAlphaArgs &a, int maps, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_alpha_gamma_fwd(const AlphaGammaArgs &a, int maps, hipStream_t st) {
+hipError_t launch_alpha_gamma_fwd(const AlphaGammaArgs &a, int maps, hipStream_t st, const ScaleRefs *refs) {
     if (a.Nh < 1 || a.Nh > kMaxK || a.Lj < 1 || 2 * a.Nh * a.Lj > kAlphaGammaCoeffs || a.T < 1 || a.nb < 1 || maps < 1)
         return hipErrorInvalidValue;
     const size_t plane = (size_t)a.nb * a.T;
     const size_t pair_bytes = a.f32 ? 8 : 16;
+    // (the scales of refs start whole planes into W)
     const bool pair = a.T % 2 == 1 && plane % 2 == 0 && (maps == 1 || a.s_w % 2 == 0) &&
                       ((uintptr_t)a.wout % pair_bytes) == 0;
-    const dim3 grid((unsigned)(((pair ? a.T / 2 + 1 : a.T) + 255) / 256), (unsigned)a.nb, (unsigned)maps);
-    if (t_rec) return rec_job(pkind(PS_AGF, a.f32, a.Nh, pair ? 1 : 0), (long long)grid.x * a.nb, maps, 256, a);
+    const ScaleRefs r = refs ? *refs : ScaleRefs{1, {{0, a.Lj, 0, 0, nullptr}}};
+    for (int i = 0; i < r.n; ++i)
+        if (r.s[i].Lj < 1 || r.s[i].Lj > a.Lj || r.s[i].out_off % (long long)plane) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(((pair ? a.T / 2 + 1 : a.T) + 255) / 256), (unsigned)a.nb, (unsigned)(maps * r.n));
+    if (t_rec) return refs ? hipErrorNotSupported : rec_job(pkind(PS_AGF, a.f32, a.Nh, pair ? 1 : 0), (long long)grid.x * a.nb, maps, 256, a);
     switch (a.Nh * 4 + (pair ? 2 : 0) + (a.f32 ? 1 : 0)) {
 #define S2DW_AG_CASE(NH)                                                                               \
-    case 4 * NH: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<false, NH, double2>), grid, dim3(256), 0, st, a); break; \
-    case 4 * NH + 1: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<false, NH, float2>), grid, dim3(256), 0, st, a); break; \
-    case 4 * NH + 2: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<true, NH, double2>), grid, dim3(256), 0, st, a); break; \
-    case 4 * NH + 3: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<true, NH, float2>), grid, dim3(256), 0, st, a); break;
+    case 4 * NH: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<false, NH, double2>), grid, dim3(256), 0, st, a, r); break; \
+    case 4 * NH + 1: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<false, NH, float2>), grid, dim3(256), 0, st, a, r); break; \
+    case 4 * NH + 2: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<true, NH, double2>), grid, dim3(256), 0, st, a, r); break; \
+    case 4 * NH + 3: hipLaunchKernelGGL((alpha_gamma_fwd_kernel<true, NH, float2>), grid, dim3(256), 0, st, a, r); break;
         S2DW_AG_CASE(1)
         S2DW_AG_CASE(2)
         S2DW_AG_CASE(3)

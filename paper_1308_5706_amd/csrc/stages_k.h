@@ -62,6 +62,24 @@ __device__ __forceinline__ C zero2() { return mk<C>(0, 0); }
 template <class C>
 __device__ __forceinline__ C to_c(double2 v) { return mk<C>((real_t<C>)v.x, (real_t<C>)v.y); }
 
+// The scale of a launch over several that workgroup bx belongs to.
+__device__ __forceinline__ int ref_of(const ScaleRefs &r, int bx) {
+    int s = 0;
+    for (int i = 1; i < r.n; ++i)
+        if (bx >= r.s[i].first) s = i;
+    return s;
+}
+
+// The arguments of one of them (in and out in elements of type I and O).
+template <class I, class O>
+__device__ __forceinline__ StageArgs at_scale(StageArgs a, const ScaleRef &r) {
+    a.Lj = r.Lj;
+    a.hh = r.hh;
+    a.in = (const I *)a.in + r.in_off;
+    a.out = (O *)a.out + r.out_off;
+    return a;
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------- analysis: beta (Eq. 29)
@@ -97,9 +115,10 @@ __device__ __forceinline__ void beta_fwd_fft_body(const StageArgs &a, int bx, in
 }
 
 template <class C, int P>
-__global__ void __launch_bounds__(P / kRM, kMinWaves) beta_fwd_fft_kernel(const StageArgs a) {
+__global__ void __launch_bounds__(P / kRM, kMinWaves) beta_fwd_fft_kernel(const StageArgs a, const ScaleRefs refs) {
     __shared__ C buf[fft::padded(P)];
-    beta_fwd_fft_body<C, P>(a, blockIdx.x, blockIdx.y, threadIdx.x, buf);
+    const ScaleRef &r = refs.s[ref_of(refs, blockIdx.x)];
+    beta_fwd_fft_body<C, P>(at_scale<double2, C>(a, r), blockIdx.x - r.first, blockIdx.y, threadIdx.x, buf);
 }
 
 // Two columns (n, m0) and (n, m0 + 1) of the equiangular grid in one transform.  With
@@ -151,9 +170,10 @@ __device__ __forceinline__ void beta_fwd_pair_body(const StageArgs &a, int bx, i
 }
 
 template <class C, int P>
-__global__ void __launch_bounds__(P / kRM, kMinWaves) beta_fwd_pair_kernel(const StageArgs a) {
+__global__ void __launch_bounds__(P / kRM, kMinWaves) beta_fwd_pair_kernel(const StageArgs a, const ScaleRefs refs) {
     __shared__ C buf[fft::padded(P)];
-    beta_fwd_pair_body<C, P>(a, blockIdx.x, blockIdx.y, threadIdx.x, buf);
+    const ScaleRef &r = refs.s[ref_of(refs, blockIdx.x)];
+    beta_fwd_pair_body<C, P>(at_scale<double2, C>(a, r), blockIdx.x - r.first, blockIdx.y, threadIdx.x, buf);
 }
 
 // Waves per SIMD the prime-factor kernels are built for: two eight-wave workgroups per CU
@@ -895,9 +915,15 @@ __device__ __forceinline__ void alpha_gamma_fwd_body(const AlphaGammaArgs &a, in
 }
 
 template <bool PAIR, int NH, class C>
-__global__ void __launch_bounds__(256) alpha_gamma_fwd_kernel(const AlphaGammaArgs a) {
+__global__ void __launch_bounds__(256) alpha_gamma_fwd_kernel(const AlphaGammaArgs a, const ScaleRefs refs) {
     __shared__ double2 cs[kAlphaGammaCoeffs];  // [k][side][m]: side 0 row n, side 1 row -n
-    alpha_gamma_fwd_body<PAIR, NH, C>(a, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x, cs);
+    const int map = blockIdx.z / refs.n;
+    const ScaleRef &r = refs.s[blockIdx.z - map * refs.n];
+    AlphaGammaArgs s = a;
+    s.Lj = r.Lj;
+    s.in = (const C *)a.in + r.in_off;
+    s.wout = (real_t<C> *)a.wout + r.out_off;
+    alpha_gamma_fwd_body<PAIR, NH, C>(s, blockIdx.x, blockIdx.y, map, threadIdx.x, cs);
 }
 
 // Coarse scales of the synthesis: both quadratures at once, ring by ring, without X (FP64
@@ -1000,10 +1026,16 @@ __device__ __forceinline__ void gamma_alpha_adj_body(const GammaAlphaArgs &a, in
 }
 
 template <int NH, class C>
-__global__ void __launch_bounds__(256) gamma_alpha_adj_kernel(const GammaAlphaArgs a) {
+__global__ void __launch_bounds__(256) gamma_alpha_adj_kernel(const GammaAlphaArgs a, const ScaleRefs refs) {
     __shared__ double2 xs[NH][256];
     __shared__ double2 red[2][256];
-    gamma_alpha_adj_body<NH, C>(a, blockIdx.x, blockIdx.y, threadIdx.x, xs, red);
+    const int map = blockIdx.y / refs.n;
+    const ScaleRef &r = refs.s[blockIdx.y - map * refs.n];
+    GammaAlphaArgs s = a;
+    s.Lj = r.Lj;
+    s.win = (const real_t<C> *)a.win + r.in_off;
+    s.out = (C *)a.out + r.out_off;
+    gamma_alpha_adj_body<NH, C>(s, blockIdx.x, map, threadIdx.x, xs, red);
 }
 
 // Complex signals: complex map z = real maps 2z (real part of f) and 2z + 1 (imaginary part);
@@ -1308,12 +1340,15 @@ __global__ void __launch_bounds__(P / kRM, kMinWaves) beta_adj_multi_kernel(cons
 // then the fold (3).  Since m' theta_t = (m'^2 + m' + t^2 - (m' - t)^2) pi/Tb, the sum is one
 // chirp convolution per column: V(m') = conj(cpp(m')) sum_t [q_t G_t conj(csq_t)] e^{i pi (m'-t)^2/Tb}.
 template <class C, int P>
-__global__ void __launch_bounds__(P / kRM, kMinWaves) beta_adj_dh_kernel(const StageArgs a) {
+__global__ void __launch_bounds__(P / kRM, kMinWaves) beta_adj_dh_kernel(const StageArgs all,
+                                                                          const ScaleRefs refs) {
     __shared__ C buf[fft::padded(P)];
     constexpr int NT = P / kRM;
     const int tid = threadIdx.x;
-    const int Lj = a.Lj, L = a.L, N = a.N, nb = a.nb;
-    const int k = blockIdx.x / Lj, m = blockIdx.x - (blockIdx.x / Lj) * Lj;
+    const ScaleRef &sr = refs.s[ref_of(refs, blockIdx.x)];
+    const StageArgs a = at_scale<C, C>(all, sr);
+    const int Lj = a.Lj, L = a.L, N = a.N, nb = a.nb, bx = blockIdx.x - sr.first;
+    const int k = bx / Lj, m = bx - k * Lj;
     int n = 0;
 #pragma unroll
     for (int kk = 0; kk < kMaxK; ++kk)
