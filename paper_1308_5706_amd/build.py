@@ -12,7 +12,7 @@ OUT = os.path.join(HERE, "libs2dw.so")
 BUILD = os.path.join(HERE, "_build")
 
 SOURCES = ["persist.hip", "api.cpp", "tables.cpp", "wigner.hip", "stages.hip", "fused_fwd.hip", "fused_adj.hip",
-           "misc.hip"]
+           "fused_fwd_cx.hip", "fused_adj_cx.hip", "misc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("S2DW_ARCH", "gfx950")

@@ -1130,7 +1130,8 @@ bool fuse_adj(const Plan &P, const Shape &sh, int f32, int T) {
 // scale by scale: 0.499 ms against 0.526); the mixed path keeps those, whose FP32 rounding is part
 // of its results.
 bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
-    if (t_rec || cx || !fused_fft(P.PB[j], P.Nh) || pfa_length(2 * P.Lg[j] - 1)) return false;
+    const int T = 2 * P.Lg[j] - 1;
+    if (t_rec || pfa_length(T) || !fused_fft(P.PB[j], T, P.Nh, cx)) return false;
     // while stages are timed, the alpha and gamma sums of the smallest maps (in no size blocked, so
     // with the same results) stay apart, each with a time of its own
     if (g_prof.on && !t_no_events && P.Lg[j] < 64) return false;
@@ -1141,8 +1142,17 @@ bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
 // launches per scale, the calls up to L of a few hundred spend more time between launches and in
 // their last waves than in full ones (analysis L = 64, N = 3: 21 launches, 113 us, against 8 and
 // 48 us).  The call that allocates nothing and the persistent program keep a scale's room.
-bool side_by_side(const Plan &P, const Work &w, int maps, bool cx) {
-    return !t_rec && !cx && P.s_Ubs > 0 && maps <= side_maps(P) && (size_t)maps * P.s_Ubs <= w.n_Ub;
+bool side_by_side(const Plan &P, const Work &w, int maps) {
+    return !t_rec && P.s_Ubs > 0 && maps <= side_maps(P) && (size_t)maps * P.s_Ubs <= w.n_Ub;
+}
+
+hipError_t fused_fwd(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, bool cx, hipStream_t st) {
+    return cx ? launch_fused_fft<true, 2>(a, refs, nwg, P, maps / 2, st)
+              : launch_fused_fft<true, 1>(a, refs, nwg, P, maps, st);
+}
+hipError_t fused_adj(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, bool cx, hipStream_t st) {
+    return cx ? launch_fused_fft<false, 2>(a, refs, nwg, P, maps / 2, st)
+              : launch_fused_fft<false, 1>(a, refs, nwg, P, maps, st);
 }
 
 // Scales that share a launch: same kernel (kind) and transform size.
@@ -1215,7 +1225,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     const size_t per_map = P.woff[P.S];  // elements of one W (complex ones with cx)
     const size_t ew = (f32 ? 4 : 8) * (cx ? 2 : 1);
     const int wmaps = cx ? maps / 2 : maps;
-    const bool side = side_by_side(P, w, maps, cx);
+    const bool side = side_by_side(P, w, maps);
     const size_t s_Ub = side ? P.s_Ubs : P.s_Ub;
     std::vector<RefGroup> direct, fused;  // scales whose alpha and gamma sums follow the loop
     StageArgs sb{};                       // the arguments all scales share (side by side)
@@ -1362,7 +1372,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             d.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
             d.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
             Stage sg("alpha_gamma_fwd", st);
-            S2DW_CHECK_HIP(launch_alpha_gamma_fwd_fft(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, st));
+            S2DW_CHECK_HIP(fused_fwd(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, cx, st));
             continue;
         }
         StageArgs c = b;
@@ -1410,7 +1420,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     for (const RefGroup &g : fused) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
         Stage sg("alpha_gamma_fwd", st, g.refs.n);
-        S2DW_CHECK_HIP(launch_alpha_gamma_fwd_fft(sb, g.refs, g.nwg, g.size, maps, st));
+        S2DW_CHECK_HIP(fused_fwd(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }
     for (const RefGroup &g : direct) {
         AlphaGammaArgs d{};
@@ -1442,7 +1452,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
     const int L = P.L, N = P.ht.N;
     const size_t per_map = P.woff[P.S];
     const size_t ew = (f32 ? 4 : 8) * (cx ? 2 : 1);
-    const bool side = side_by_side(P, w, maps, cx);
+    const bool side = side_by_side(P, w, maps);
     const size_t s_Ub = side ? P.s_Ubs : P.s_Ub;
     StageArgs sb{};
     GammaAlphaArgs sd{};
@@ -1496,7 +1506,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
                 sb = d;
             } else {
                 Stage sg("gamma_alpha_adj", st);
-                S2DW_CHECK_HIP(launch_gamma_alpha_adj_fft(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, st));
+                S2DW_CHECK_HIP(fused_adj(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, cx, st));
             }
         } else if (fused_pfa) {
             StageArgs d{};
@@ -1615,7 +1625,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
     for (const RefGroup &g : fusedg) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
         Stage sg("gamma_alpha_adj", st, g.refs.n);
-        S2DW_CHECK_HIP(launch_gamma_alpha_adj_fft(sb, g.refs, g.nwg, g.size, maps, st));
+        S2DW_CHECK_HIP(fused_adj(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }
     for (const RefGroup &g : direct) {
         Stage sg("gamma_alpha_adj", st, g.refs.n);

@@ -1,0 +1,6 @@
+// The fused alpha and gamma kernels (fused_k.h) of the synthesis, complex signals.
+#include "fused_k.h"
+
+namespace s2dw {
+template hipError_t launch_fused_fft<false, 2>(const StageArgs &, const ScaleRefs &, int, int, int, hipStream_t);
+}  // namespace s2dw

@@ -117,11 +117,13 @@ hipError_t launch_beta_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t 
 hipError_t launch_beta_fwd_pair(const StageArgs &a, int P, int maps, hipStream_t st, const ScaleRefs *refs = nullptr,
                                 int nwg = 0);
 // The alpha and gamma passes of one or more scales in one kernel with chirp convolutions of size P
-// (real signals, Nh <= 4, P >= 128): analysis Ub -> W, synthesis W -> G (scaled by a.scale);
-// 8 ceil(nb / 8) workgroups per scale (fused_k.h).
-bool fused_fft(int P, int Nh);
-hipError_t launch_alpha_gamma_fwd_fft(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, hipStream_t st);
-hipError_t launch_gamma_alpha_adj_fft(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, hipStream_t st);
+// (fused_k.h): analysis (FWD) Ub -> W, synthesis W -> G (scaled by a.scale), of real signals
+// (M = 1) or complex ones (M = 2: their maps 2z and 2z + 1, W as (re, im) pairs with s_w and the
+// offsets in complex elements); 8 ceil(nb / 8) workgroups per scale and signal.  fused_fft:
+// whether there is such a kernel for T samples and Nh orders.
+bool fused_fft(int P, int T, int Nh, bool cx);
+template <bool FWD, int M>
+hipError_t launch_fused_fft(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int signals, hipStream_t st);
 hipError_t launch_alpha_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_adj_fft(const StageArgs &a, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_fwd_blk(const StageArgs &a, int P, int maps, hipStream_t st);

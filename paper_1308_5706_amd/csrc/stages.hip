@@ -152,7 +152,11 @@ bool pfa_fused(int T, int Nh) {
     return false;
 }
 
-bool fused_fft(int P, int Nh) { return Nh >= 1 && Nh <= 4 && P >= 128 && P <= 8192; }
+bool fused_fft(int P, int T, int Nh, bool cx) {
+    if (Nh < 1 || Nh > 4 || P < 128 || P > 8192) return false;
+    // (a complex signal's orders would not fit the registers)
+    return !(cx && Nh > 2 && (P == 8192 || (P == 4096 && T > P / 2)));
+}
 
 #define S2DW_FUSED_CASE(KER, LN, NH)                                                                     \
     case NH:                                                                                             \

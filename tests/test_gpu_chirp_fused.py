@@ -1,6 +1,7 @@
 """The fused alpha and gamma kernels with chirp convolutions, and scales that go through a stage
-together, against the separate passes: a real signal analysed and synthesised as a complex one
-(reality=False) takes two-pass kernels, one scale at a time.
+together: a real signal against the same signal as a complex one (reality=False: the kernel that
+takes two maps, other orders side by side), and both against the persistent executor, which runs
+the separate passes one scale at a time.
 
 Sizes: every transform size (128 .. 8192), 1 .. 4 orders side by side or in several passes, four
 and eight samples per thread, the last band-limit of a size and the first of the next, scales
@@ -68,3 +69,20 @@ def test_batches_beside_and_beyond_the_shared_workspace():
     finally:
         s2dw.profile(False)
     assert torch.equal(W[1], W2) and torch.equal(b[1], b2)
+
+
+@pytest.mark.parametrize("L,N,J_min", [(18, 4, 0), (33, 8, 0), (64, 3, 0), (65, 7, 1), (130, 1, 2), (257, 8, 4), (500, 5, 6)])
+def test_complex_signals_equal_two_real_ones_in_separate_passes(L, N, J_min):
+    print(f"L={L} N={N} J_min={J_min}", flush=True)
+    a, b = real_signal(L, 1), real_signal(L, 2)
+    ab = torch.stack([a, b])
+    for prec, tol in TOL.items():
+        W, Wp = s2dw.analysis(a + 1j * b, L, N, 2.0, J_min, precision=prec, reality=False)
+        (Wr, Wpr), = s2dw.analysis_persistent([(L, N, 2.0, J_min, ab)], precision=prec)
+        assert rel(W.real, Wr[0]) < tol and rel(W.imag, Wr[1]) < tol
+        assert rel(Wp, Wpr[0] + 1j * Wpr[1]) < tol
+        c = s2dw.synthesis(W, Wp, L, N, 2.0, J_min, precision=prec, reality=False)
+        cr, = s2dw.synthesis_persistent([(L, N, 2.0, J_min, Wr, Wpr)], precision=prec)
+        assert rel(c, cr[0] + 1j * cr[1]) < tol
+        W2 = s2dw.analysis(b, L, N, 2.0, J_min, precision=prec)[0]
+        assert rel(W2, Wr[1]) < tol
