@@ -126,7 +126,20 @@ def fused_scales(L, N, Ljs, mixed=False):
     return fwd, adj
 
 
-def stage_units(kappa, L, N, T, fused=True, fused_adj=True, pfa=None, mixed=False):
+def taken_scales(L, N, Ljs, mixed=False):
+    """The scales (by band-limit) whose alpha and gamma sums the library takes in one kernel:
+    (analysis, synthesis).  With at most four orders n >= 0 every scale at the chirp lengths; at
+    the prime-factor lengths those of fused_scales and those with blocked transforms."""
+    if N - N // 2 > 4:
+        return [], []
+    if 2 * L - 1 not in (2047, 4095):
+        return list(Ljs), list(Ljs)
+    fw, ad = fused_scales(L, N, Ljs, mixed)
+    blk = [Lj for Lj in Ljs if blocked_alpha(L, Lj)]
+    return [Lj for Lj in Ljs if Lj in fw or Lj in blk], [Lj for Lj in Ljs if Lj in ad or Lj in blk]
+
+
+def stage_units(kappa, L, N, T, fused=True, fused_adj=True, pfa=None, mixed=False, taken=None):
     """Algorithmic work of each stage per step (one map), summed over the scales.
 
     Wigner stages (one launch per direction): 5 FLOP per term of the l-sum / m'-contraction
@@ -146,7 +159,8 @@ def stage_units(kappa, L, N, T, fused=True, fused_adj=True, pfa=None, mixed=Fals
                 gamma_adj and alpha_adj)  W 8 G L T in,  G 16 N Lj L out
     With pfa (default: pfa_fused(L, N)) the scales that fused_scales names take the fused
     prime-factor kernels, also counted as alpha_gamma_fwd and gamma_alpha_adj, with the same
-    bytes and, as FLOP, the alpha DFTs of its rings.
+    bytes and, as FLOP, the alpha DFTs of its rings.  taken (taken_scales): all the scales whose
+    alpha and gamma sums go in one kernel, in place of those.
     and, for the four Fourier stages, FLOP with a length-n complex DFT counted as an FFT,
     5 n log2 n, whatever way it is computed:
       beta_fwd  N Lj columns, one length-T DFT each
@@ -166,7 +180,7 @@ def stage_units(kappa, L, N, T, fused=True, fused_adj=True, pfa=None, mixed=Fals
             Ljs.append(max(nz) + 1)
     if pfa is None:
         pfa = pfa_fused(L, N)
-    fw, ad = fused_scales(L, N, Ljs, mixed) if pfa else ([], [])
+    fw, ad = taken(L, N, Ljs, mixed) if taken else fused_scales(L, N, Ljs, mixed) if pfa else ([], [])
     direct = [Lj for Lj in Ljs if fused and direct_alpha_gamma(N, Lj)]
     direct_adj = [Lj for Lj in Ljs if fused_adj and direct_alpha_gamma(N, Lj)]
     pf = [Lj for Lj in Ljs if Lj in fw and Lj not in direct]
@@ -576,7 +590,7 @@ def main():
     # roofline of that kernel, timed with HIP events during the timed steps
     kappa, _, _ = s2dw.wavelet_tables(L, N, lam, J_min)
     T = wigner_terms(kappa, N)
-    units = stage_units(kappa, L, N, T, fused_adj=prec == "fp64", mixed=prec != "fp64")
+    units = stage_units(kappa, L, N, T, fused_adj=prec == "fp64", mixed=prec != "fp64", taken=taken_scales)
     roof = roofline(dom, live[dom], units)
     traffic = None
     try:

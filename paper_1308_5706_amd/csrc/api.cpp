@@ -1126,9 +1126,10 @@ bool fuse_adj(const Plan &P, const Shape &sh, int f32, int T) {
 }
 
 // Whether scale j takes the fused alpha and gamma kernel with chirp convolutions (fused_k.h).
-// FP64 also in place of the blocked transforms (analysis L = 512, N = 4 on the Driscoll-Healy grid,
-// scale by scale: 0.499 ms against 0.526); the mixed path keeps those, whose FP32 rounding is part
-// of its results.
+// FP64 also in place of blocked transforms, which are not cheaper there (fused_blk.hip: L = 421,
+// N = 6, analysis 0.295 ms against 0.307, synthesis 0.407 against 0.415; 0.361 against 0.354 on the
+// Driscoll-Healy grid at L = 512, N = 4); the mixed path keeps those, whose FP32 rounding is part of
+// its results.
 bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
     const int T = 2 * P.Lg[j] - 1;
     if (t_rec || pfa_length(T) || !fused_fft(P.PB[j], T, P.Nh, cx)) return false;
@@ -1136,6 +1137,13 @@ bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
     // with the same results) stay apart, each with a time of its own
     if (g_prof.on && !t_no_events && P.Lg[j] < 64) return false;
     return P.nblkb[j] <= 1 || !f32;
+}
+
+// Whether scale j, not taken by fuse_fft, takes the fused alpha and gamma kernel with blocked
+// transforms (fused_blk.hip): against the two passes, round trip L = 700, N = 8, mixed 1.50 ms
+// against 1.58, analysis L = 1024, N = 8 2.01 against 2.05 (FP64).
+bool fuse_blk(const Plan &P, const Shape &sh, int j, bool cx) {
+    return !t_rec && !cx && P.nblkb[j] > 1 && P.Nh <= 4 && !(sh.fuse == 0 && pfa_length(2 * P.Lg[j] - 1));
 }
 
 // Whether the scales of this call go through each stage together (kSideBytes): as separate
@@ -1160,10 +1168,11 @@ struct RefGroup {
     int kind, size, nwg;
     ScaleRefs refs;
 };
-void add_ref(std::vector<RefGroup> &v, int kind, int size, int nwg, int Lj, size_t in_off, size_t out_off, const void *hh) {
+void add_ref(std::vector<RefGroup> &v, int kind, int size, int nwg, int Lj, size_t in_off, size_t out_off, const void *hh,
+             int B = 0, int nblk = 0) {
     if (v.empty() || v.back().kind != kind || v.back().size != size) v.push_back(RefGroup{kind, size, 0, {}});
     RefGroup &g = v.back();
-    g.refs.s[g.refs.n++] = ScaleRef{g.nwg, Lj, (long long)in_off, (long long)out_off, hh};
+    g.refs.s[g.refs.n++] = ScaleRef{g.nwg, Lj, (long long)in_off, (long long)out_off, hh, B, nblk};
     g.nwg += nwg;
 }
 
@@ -1262,6 +1271,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
         sb.wout = W;
         sb.s_w = per_map;
         sb.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
+        sb.eph = f32 ? (const void *)gtab.ephf : gtab.eph;
         sb.tg = f32 ? (const void *)P.tgff : P.tgf;
         sb.G = P.ng;
     }
@@ -1372,7 +1382,29 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             d.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
             d.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
             Stage sg("alpha_gamma_fwd", st);
-            S2DW_CHECK_HIP(fused_fwd(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, cx, st));
+            S2DW_CHECK_HIP(fused_fwd(d, ScaleRefs{1, {{0, Lj, 0, 0, hh, 0, 0}}}, nwg, P.PB[j], maps, cx, st));
+            continue;
+        }
+        if (fuse_blk(P, sh, j, cx)) {
+            const int nwg = 8 * ((b.nb + 7) / 8);
+            const void *hh = f32 ? (const void *)P.hBbf[j] : P.hBb[j];
+            if (side) {
+                add_ref(fused, 1, P.PBb[j], nwg, Lj, P.uboff[j], P.woff[j], hh, P.Bb[j], P.nblkb[j]);
+                continue;
+            }
+            StageArgs d = b;
+            d.in = ubj;
+            d.s_in = s_Ub;
+            d.wout = Wj;
+            d.s_w = per_map;
+            d.tg = f32 ? (const void *)P.tgff : P.tgf;
+            d.G = P.ng;
+            d.tw = f32 ? (const void *)P.twPf[P.PBb[j]] : P.twP[P.PBb[j]];
+            d.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
+            d.eph = f32 ? (const void *)gtab.ephf : gtab.eph;
+            Stage sg("alpha_gamma_fwd", st);
+            S2DW_CHECK_HIP(launch_fused_blk<true>(d, ScaleRefs{1, {{0, Lj, 0, 0, hh, P.Bb[j], P.nblkb[j]}}}, nwg, P.PBb[j],
+                                                  maps, st));
             continue;
         }
         StageArgs c = b;
@@ -1420,7 +1452,8 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     for (const RefGroup &g : fused) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
         Stage sg("alpha_gamma_fwd", st, g.refs.n);
-        S2DW_CHECK_HIP(fused_fwd(sb, g.refs, g.nwg, g.size, maps, cx, st));
+        S2DW_CHECK_HIP(g.kind ? launch_fused_blk<true>(sb, g.refs, g.nwg, g.size, maps, st)
+                              : fused_fwd(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }
     for (const RefGroup &g : direct) {
         AlphaGammaArgs d{};
@@ -1482,10 +1515,12 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
         // larger Lj, where the FP32 passes of the mixed path are cheaper
         const bool fused = direct_alpha_gamma(P.Nh, P.ng, Lj, cx) && !f32;
         const bool fused_pfa = !fused && gtab.pcs && !cx && pfa_fused(M, P.Nh) && fuse_adj(P, sh, f32, M);
-        const bool fused_ch = !fused && fuse_fft(P, f32, j, cx);
+        const bool unblk = !fused && fuse_fft(P, f32, j, cx), blk = !fused && !fused_pfa && !unblk && fuse_blk(P, sh, j, cx);
+        const bool fused_ch = unblk || blk;
         if (fused_ch) {
-            const int nwg = 8 * ((g.L + 7) / 8);
-            const void *hh = f32 ? (const void *)P.hCf[j] : P.hC[j];
+            const int nwg = 8 * ((g.L + 7) / 8), size = blk ? P.PBb[j] : P.PB[j];
+            const int B = blk ? P.Bb[j] : 0, nblk = blk ? P.nblkb[j] : 0;
+            const void *hh = blk ? (f32 ? (const void *)P.hCbf[j] : P.hCb[j]) : (f32 ? (const void *)P.hCf[j] : P.hC[j]);
             StageArgs d{};
             d.f32 = f32;
             d.win = side ? W : Wj;
@@ -1500,13 +1535,16 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             d.N = N;
             d.Nh = P.Nh;
             d.scale = qscale;
-            d.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
+            d.eph = f32 ? (const void *)gtab.ephf : gtab.eph;
+            d.tw = f32 ? (const void *)P.twPf[size] : P.twP[size];
             if (side) {
-                add_ref(fusedg, 0, P.PB[j], nwg, Lj, P.woff[j], uo, hh);
+                add_ref(fusedg, blk ? 1 : 0, size, nwg, Lj, P.woff[j], uo, hh, B, nblk);
                 sb = d;
             } else {
+                const ScaleRefs refs{1, {{0, Lj, 0, 0, hh, B, nblk}}};
                 Stage sg("gamma_alpha_adj", st);
-                S2DW_CHECK_HIP(fused_adj(d, ScaleRefs{1, {{0, Lj, 0, 0, hh}}}, nwg, P.PB[j], maps, cx, st));
+                S2DW_CHECK_HIP(blk ? launch_fused_blk<false>(d, refs, nwg, size, maps, st)
+                                   : fused_adj(d, refs, nwg, size, maps, cx, st));
             }
         } else if (fused_pfa) {
             StageArgs d{};
@@ -1625,7 +1663,8 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
     for (const RefGroup &g : fusedg) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
         Stage sg("gamma_alpha_adj", st, g.refs.n);
-        S2DW_CHECK_HIP(fused_adj(sb, g.refs, g.nwg, g.size, maps, cx, st));
+        S2DW_CHECK_HIP(g.kind ? launch_fused_blk<false>(sb, g.refs, g.nwg, g.size, maps, st)
+                              : fused_adj(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }
     for (const RefGroup &g : direct) {
         Stage sg("gamma_alpha_adj", st, g.refs.n);

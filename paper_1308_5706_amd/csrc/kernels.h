@@ -99,11 +99,12 @@ struct StageArgs {
 };
 // The scales of one launch (same grid, same transform size): the first workgroup of each, its
 // band-limit, the element offsets of its input and output from the launch's in and out (W: from
-// win, wout, in real elements), and its spectrum.
+// win, wout, in their elements), and its spectrum.
 struct ScaleRef {
     int first, Lj;
     long long in_off, out_off;
     const void *hh;
+    int B, nblk;  // blocked alpha transforms only: samples per block, blocks
 };
 struct ScaleRefs {
     int n;
@@ -124,6 +125,10 @@ hipError_t launch_beta_fwd_pair(const StageArgs &a, int P, int maps, hipStream_t
 bool fused_fft(int P, int T, int Nh, bool cx);
 template <bool FWD, int M>
 hipError_t launch_fused_fft(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int signals, hipStream_t st);
+// The same for scales with blocked alpha transforms of size P = 512, 1024 or 2048 (real signals,
+// Nh <= 4; fused_blk.hip).
+template <bool FWD>
+hipError_t launch_fused_blk(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_fwd_fft(const StageArgs &a, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_adj_fft(const StageArgs &a, int P, int maps, hipStream_t st);
 hipError_t launch_alpha_fwd_blk(const StageArgs &a, int P, int maps, hipStream_t st);

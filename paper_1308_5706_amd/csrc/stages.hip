@@ -31,7 +31,7 @@ namespace s2dw {
     }
 
 // The launch's one scale as a table.
-static ScaleRefs one_scale(const StageArgs &a) { return ScaleRefs{1, {{0, a.Lj, 0, 0, a.hh}}}; }
+static ScaleRefs one_scale(const StageArgs &a) { return ScaleRefs{1, {{0, a.Lj, 0, 0, a.hh, 0, 0}}}; }
 
 #define S2DW_R_CASE(C, KER, PV) \
     case PV: hipLaunchKernelGGL((KER<C, PV>), dim3(nwg, maps), dim3(PV / kRM), 0, st, a, r); break;
@@ -283,7 +283,7 @@ hipError_t launch_gamma_alpha_adj(const GammaAlphaArgs &a, int maps, hipStream_t
         a.G > 4 * a.Nh - 1 || maps < 1)
         return hipErrorInvalidValue;
     if (t_rec) return refs ? hipErrorNotSupported : rec_job(pkind(PS_GAA, a.f32, a.Nh), a.nb, maps, 256, a);
-    const ScaleRefs r = refs ? *refs : ScaleRefs{1, {{0, a.Lj, 0, 0, nullptr}}};
+    const ScaleRefs r = refs ? *refs : ScaleRefs{1, {{0, a.Lj, 0, 0, nullptr, 0, 0}}};
     for (int i = 0; i < r.n; ++i)
         if (r.s[i].Lj < 1 || r.s[i].Lj > a.Lj) return hipErrorInvalidValue;
     const dim3 grid((unsigned)a.nb, (unsigned)(maps * r.n));
@@ -313,7 +313,7 @@ hipError_t launch_alpha_gamma_fwd(const AlphaGammaArgs &a, int maps, hipStream_t
     // (the scales of refs start whole planes into W)
     const bool pair = a.T % 2 == 1 && plane % 2 == 0 && (maps == 1 || a.s_w % 2 == 0) &&
                       ((uintptr_t)a.wout % pair_bytes) == 0;
-    const ScaleRefs r = refs ? *refs : ScaleRefs{1, {{0, a.Lj, 0, 0, nullptr}}};
+    const ScaleRefs r = refs ? *refs : ScaleRefs{1, {{0, a.Lj, 0, 0, nullptr, 0, 0}}};
     for (int i = 0; i < r.n; ++i)
         if (r.s[i].Lj < 1 || r.s[i].Lj > a.Lj || r.s[i].out_off % (long long)plane) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(((pair ? a.T / 2 + 1 : a.T) + 255) / 256), (unsigned)a.nb, (unsigned)(maps * r.n));

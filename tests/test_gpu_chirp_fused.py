@@ -5,7 +5,7 @@ the separate passes one scale at a time.
 
 Sizes: every transform size (128 .. 8192), 1 .. 4 orders side by side or in several passes, four
 and eight samples per thread, the last band-limit of a size and the first of the next, scales
-too large to go together (L = 1500, N = 8), both full grids and the multiresolution one."""
+too large to go together (L = 1500, N = 8), blocked transforms (L = 512 and more), both full grids and the multiresolution one."""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +39,7 @@ def rel(a, b):
 @pytest.mark.parametrize("L,N,J_min,grid", [
     (16, 3, 0, "mw"), (20, 3, 0, "mw"), (32, 8, 0, "mw"), (33, 2, 0, "mw"), (64, 7, 0, "mw"), (65, 5, 0, "mw"),
     (128, 1, 0, "mw"), (129, 8, 1, "mw"), (256, 6, 2, "mw"), (300, 6, 0, "mw"), (513, 3, 3, "mw"), (700, 8, 4, "mw"),
+    (1024, 7, 5, "mw"), (1024, 2, 5, "mw"), (600, 5, 3, "mw"),
     (1100, 7, 7, "mw"), (1500, 8, 9, "mw"), (2047, 2, 9, "mw"), (31, 4, 0, "dh"), (150, 8, 2, "dh"), (512, 3, 4, "dh"),
     (90, 7, 0, "multires"), (300, 4, 2, "multires")])
 def test_fused_equals_separate_passes(L, N, J_min, grid):
