@@ -44,7 +44,7 @@ alpha_gamma_fwd_blk_kernel(const StageArgs a, const ScaleRefs refs) {
         base[s] = ok ? c : zero2<C>();
     }
     R *__restrict__ W = (R *)a.wout + blockIdx.y * a.s_w + sr.out_off + (size_t)b * T;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     const size_t plane = (size_t)nb * T;
     C *col = cols[np];
     for (int k = 0; k < nblk; ++k) {
@@ -64,15 +64,12 @@ alpha_gamma_fwd_blk_kernel(const StageArgs a, const ScaleRefs refs) {
             C y[NH];
 #pragma unroll
             for (int r = 0; r < NH; ++r) y[r] = cols[r][pad(x)];
-            for (int g = 0; g < G; ++g) {
+            for_gamma<NH>(tg, G, [&](int g, const C *w) {
                 R acc = 0;
 #pragma unroll
-                for (int r = 0; r < NH; ++r) {
-                    const C w = tg[g * NH + r];
-                    acc = fma(y[r].x, w.x, fma(-y[r].y, w.y, acc));
-                }
+                for (int r = 0; r < NH; ++r) acc = fma(y[r].x, w[r].x, fma(-y[r].y, w[r].y, acc));
                 __builtin_nontemporal_store(acc, W + g * plane + a0 + x);
-            }
+            });
         }
     }
 }
@@ -92,7 +89,7 @@ gamma_alpha_adj_blk_kernel(const StageArgs a, const ScaleRefs refs) {
     const int ni = (N / 2) + np, nj = N - 1 - ni;
     const bool zero_n = ni == nj;
     const R *__restrict__ W = (const R *)a.win + blockIdx.y * a.s_w + sr.in_off + (size_t)b * T;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     const C *__restrict__ csq = (const C *)a.csq;
     const C *__restrict__ eph = (const C *)a.eph;
     const size_t plane = (size_t)nb * T;

@@ -96,7 +96,7 @@ alpha_gamma_fwd_fft_kernel(const StageArgs a, const ScaleRefs refs) {
     }
     using WT = std::conditional_t<M == 2, C, R>;
     WT *__restrict__ W = (WT *)a.wout + blockIdx.y * a.s_w + sr.out_off + (size_t)b * T;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     const size_t plane = (size_t)nb * T;
     const int G = a.G;
 #pragma unroll
@@ -106,20 +106,18 @@ alpha_gamma_fwd_fft_kernel(const StageArgs a, const ScaleRefs refs) {
         C y[NV];
 #pragma unroll
         for (int r = 0; r < NV; ++r) y[r] = r < NW ? held[r < NW ? r : 0][k] : cols[r < NW ? 0 : r - NW][pad(x)];
-        for (int g = 0; g < G; ++g) {
+        for_gamma<NH>(tg, G, [&](int g, const C *w) {
             R acc[M];
 #pragma unroll
             for (int c = 0; c < M; ++c) acc[c] = 0;
 #pragma unroll
-            for (int r = 0; r < NH; ++r) {
-                const C w = tg[g * NH + r];
+            for (int r = 0; r < NH; ++r)
 #pragma unroll
                 for (int c = 0; c < M; ++c)
-                    acc[c] = fma(y[c * NH + r].x, w.x, fma(-y[c * NH + r].y, w.y, acc[c]));
-            }
+                    acc[c] = fma(y[c * NH + r].x, w[r].x, fma(-y[c * NH + r].y, w[r].y, acc[c]));
             if constexpr (M == 2) nt_store(mk<C>(acc[0], acc[M - 1]), W + g * plane + x);
             else __builtin_nontemporal_store(acc[0], W + g * plane + x);
-        }
+        });
     }
 }
 
@@ -139,7 +137,7 @@ gamma_alpha_adj_fft_kernel(const StageArgs a, const ScaleRefs refs) {
     if (b >= nb) return;
     using WT = std::conditional_t<M == 2, C, R>;
     const WT *__restrict__ W = (const WT *)a.win + blockIdx.y * a.s_w + sr.in_off + (size_t)b * T;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     const C *__restrict__ csq = (const C *)a.csq;
     const size_t plane = (size_t)nb * T;
     // the gamma sums of every order at the owned samples (those past the end repeat the last:

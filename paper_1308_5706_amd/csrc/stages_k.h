@@ -62,6 +62,40 @@ __device__ __forceinline__ C zero2() { return mk<C>(0, 0); }
 template <class C>
 __device__ __forceinline__ C to_c(double2 v) { return mk<C>((real_t<C>)v.x, (real_t<C>)v.y); }
 
+// A table of complex values read at indices that are the same for a whole wave, through the scalar
+// cache.  As vector loads next to the stores of W, the gamma factors of a sample waited for the
+// stores of the one before (both count in vmcnt, which falls in order): a chain of G store
+// latencies per sample, longer than everything else in the fused analysis kernels.
+template <class C>
+struct UniTab {
+    typedef const __attribute__((address_space(4))) real_t<C> *ptr;
+    ptr p;
+    __device__ __forceinline__ explicit UniTab(const void *q) : p((ptr)(uintptr_t)q) {}
+    __device__ __forceinline__ C operator[](int i) const { return mk<C>(p[2 * i], p[2 * i + 1]); }
+};
+
+// f(g, tg[g][0 .. NH - 1]) for every g < G, the factors of a few g requested together (64 scalar
+// registers), so that the other waves' work covers their latency.
+template <int NH, class C, class F>
+__device__ __forceinline__ void for_gamma(const UniTab<C> &tg, int G, F f) {
+    constexpr int U = NH >= 3 ? 2 : 4;
+    for (int g = 0; g < G; g += U) {
+        C t[U][NH];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < NH; ++r) t[u][r] = tg[min(g + u, G - 1) * NH + r];
+        // (all of them before the first use: the compiler would move each row to its use)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < NH; ++r) __asm__ volatile("" ::"s"(t[u][r].x), "s"(t[u][r].y));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u == 0 || g + u < G) f(g + u, t[u]);
+    }
+}
+
 // The scale of a launch over several that workgroup bx belongs to.
 __device__ __forceinline__ int ref_of(const ScaleRefs &r, int bx) {
     int s = 0;
@@ -472,7 +506,7 @@ __global__ void __launch_bounds__(LN::NTH, pfa_min_waves<LN>()) alpha_gamma_fwd_
         }
     }
     R *__restrict__ W = (R *)a.wout + blockIdx.y * a.s_w + (size_t)b * T;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     const size_t plane = (size_t)nb * T;
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
@@ -483,15 +517,12 @@ __global__ void __launch_bounds__(LN::NTH, pfa_min_waves<LN>()) alpha_gamma_fwd_
         for (int r = 0; r < NHOLD; ++r) y[r] = held[r][k];
 #pragma unroll
         for (int c = 0; c < NLAST; ++c) y[NHOLD + c] = buf[c * LN::CS + LN::pos_out(x)];
-        for (int g = 0; g < G; ++g) {
+        for_gamma<NH>(tg, G, [&](int g, const C *w) {
             R acc = 0;
 #pragma unroll
-            for (int r = 0; r < NH; ++r) {
-                const C w = tg[g * NH + r];
-                acc = fma(y[r].x, w.x, fma(-y[r].y, w.y, acc));
-            }
+            for (int r = 0; r < NH; ++r) acc = fma(y[r].x, w[r].x, fma(-y[r].y, w[r].y, acc));
             __builtin_nontemporal_store(acc, W + g * plane + x);  // written once, read by the synthesis
-        }
+        });
     }
 }
 
@@ -506,7 +537,7 @@ __global__ void __launch_bounds__(LN::NTH, pfa_min_waves<LN>()) gamma_alpha_adj_
     const int b = xcd_column(blockIdx.x, nb);
     if (b >= nb) return;
     const R *__restrict__ W = (const R *)a.win + blockIdx.y * a.s_w + (size_t)b * T;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     const size_t plane = (size_t)nb * T;
     // the gamma sums of rows r0 .. r0 + NR - 1 into x[0 .. NR - 1]: plane by plane, the
     // thread's KS samples of a plane loaded together
@@ -739,7 +770,7 @@ __device__ __forceinline__ void gamma_fwd_body(const GammaArgs &a, int bx, int b
     const size_t e0 = ((size_t)bx * 256 + tid) * V;
     if (e0 >= plane) return;
     const C *__restrict__ Y = (const C *)a.in + by * a.s_y;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     C y[kMaxK][V];
 #pragma unroll
     for (int k = 0; k < kMaxK; ++k)
@@ -782,7 +813,7 @@ __device__ __forceinline__ void gamma_adj_body(const GammaArgs &a, int bx, int b
     const size_t e0 = ((size_t)bx * 256 + tid) * V;
     if (e0 >= plane) return;
     const R *__restrict__ W = (const R *)a.win + by * a.s_w;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     C *__restrict__ X = (C *)a.out + by * a.s_y;
     C x[kMaxK][V];
 #pragma unroll
@@ -892,17 +923,15 @@ __device__ __forceinline__ void alpha_gamma_fwd_body(const AlphaGammaArgs &a, in
     }
     const size_t plane = (size_t)nb * T;
     R *__restrict__ W = (R *)a.wout + bz * a.s_w + (size_t)b * T + x0;
-    const double2 *__restrict__ tg = (const double2 *)a.tg;
-    for (int g = 0; g < a.G; ++g) {
+    const UniTab<double2> tg(a.tg);
+    for_gamma<NH>(tg, a.G, [&](int g, const double2 *w) {
         double acc[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = 0.0;
 #pragma unroll
-        for (int k = 0; k < NH; ++k) {
-            const double2 w = tg[g * Nh + k];
+        for (int k = 0; k < NH; ++k)
 #pragma unroll
-            for (int v = 0; v < V; ++v) acc[v] = fma(y[k][v].x, w.x, fma(-y[k][v].y, w.y, acc[v]));
-        }
+            for (int v = 0; v < V; ++v) acc[v] = fma(y[k][v].x, w[k].x, fma(-y[k][v].y, w[k].y, acc[v]));
         R *dst = W + g * plane;
         if (PAIR && ok[0] && ok[V - 1]) {
             nt_store(mk<C>((R)acc[0], (R)acc[V - 1]), (C *)dst);
@@ -911,7 +940,7 @@ __device__ __forceinline__ void alpha_gamma_fwd_body(const AlphaGammaArgs &a, in
             for (int v = 0; v < V; ++v)
                 if (ok[v]) __builtin_nontemporal_store((R)acc[v], dst + v);
         }
-    }
+    });
 }
 
 template <bool PAIR, int NH, class C>
@@ -959,7 +988,7 @@ __device__ __forceinline__ void gamma_alpha_adj_body(const GammaAlphaArgs &a, in
     const int len = (NT + H - 1) / H;
     const size_t plane = (size_t)a.nb * T;
     const R *__restrict__ Wr = (const R *)a.win + by * a.s_w + (size_t)b * T;
-    const double2 *__restrict__ tg = (const double2 *)a.tg;
+    const UniTab<double2> tg(a.tg);
     // W of the next chunk waits in registers (G <= GMAX = 4 NH - 1, since N <= 2 NH): its
     // loads are issued before the alpha sums of the current chunk
     constexpr int GMAX = 4 * NH - 1;
@@ -1049,7 +1078,7 @@ __global__ void __launch_bounds__(256) gamma_fwd_cx_kernel(const GammaArgs a) {
     if (e >= plane) return;
     const C *__restrict__ Ya = (const C *)a.in + (size_t)(2 * blockIdx.y) * a.s_y + e;
     const C *__restrict__ Yb = Ya + a.s_y;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     C ya[kMaxK], yb[kMaxK];
 #pragma unroll
     for (int k = 0; k < kMaxK; ++k)
@@ -1078,7 +1107,7 @@ __global__ void __launch_bounds__(256) gamma_adj_cx_kernel(const GammaArgs a) {
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= plane) return;
     const C *__restrict__ W = (const C *)a.win + blockIdx.y * a.s_w + e;
-    const C *__restrict__ tg = (const C *)a.tg;
+    const UniTab<C> tg(a.tg);
     C xa[kMaxK], xb[kMaxK];
 #pragma unroll
     for (int k = 0; k < kMaxK; ++k) xa[k] = xb[k] = zero2<C>();
