@@ -1222,7 +1222,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     a.segs = P.segs;
     {
         Stage sg("wigner_fwd", st);
-        const int want = sh.nfwd > 1 ? wig_fwd_slots_for(P.K, (long)(P.Lp / 64) * L * maps) : sh.fwd[0].R;
+        const int want = sh.nfwd > 1 ? wig_fwd_slots_for(P.K, (long)(P.Lp / 64) * L, maps) : sh.fwd[0].R;
         const Shape::Fwd *ft = &sh.fwd[0];
         for (int i = 1; i < sh.nfwd; ++i)
             if (sh.fwd[i].R == want) ft = &sh.fwd[i];

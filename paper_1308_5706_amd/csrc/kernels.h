@@ -56,8 +56,8 @@ struct WigAdjArgs {
     int L, Lp, group, f32;
 };
 
-// Default m' slots per wave for K carried orders and `waves` waves at one slot per wave.
-int wig_fwd_slots_for(int K, long waves);
+// Default m' slots per wave for K carried orders, `waves` waves per map at one slot each, and `maps` maps.
+int wig_fwd_slots_for(int K, long waves, int maps);
 int wig_adj_slots(int K, long waves, int f32);
 int wig_slot_options(int K, int *R);          // compiled slot counts for K (up to 3), returns how many
 hipError_t launch_wig_fwd(const WigFwdArgs &a, int K, int R, int ntiles, int maps, hipStream_t st);

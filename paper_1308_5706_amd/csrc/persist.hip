@@ -94,7 +94,7 @@ __device__ __forceinline__ void fft_item(int vb0, int gx, int tid, unsigned char
         default: break;       \
     }
 
-// The Wigner tile shapes of the executor (persist_slots: the ordinary kernels' defaults).
+// The Wigner tile shapes of the executor (persist_slots).
 #define S2DW_PERSIST_KR(CALL) \
     switch (ka * 8 + kb) {    \
         case 12: CALL(1, 4) break; \
