@@ -332,7 +332,7 @@ __device__ __forceinline__ u32x4 desc_of(const void *p) {
 __device__ __forceinline__ void load_lds16(u32x4 d, unsigned lane_off, unsigned off, unsigned lds) {
     asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(lane_off), "s"(d),
                  "s"(__builtin_amdgcn_readfirstlane(off)), "s"(__builtin_amdgcn_readfirstlane(lds))
-                 : "memory");
+                 : "m0", "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_lds() {
