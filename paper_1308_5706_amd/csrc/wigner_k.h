@@ -319,7 +319,10 @@ __device__ __forceinline__ u32x4 buf_b128(__amdgpu_buffer_rsrc_t b, unsigned lan
 // lane, lane i to LDS byte lds + 16 i.  They return in order; wait_lds<N> waits until at most N
 // vector memory operations are in flight.  (Written out because the compiler would wait for all
 // of them before the next read of LDS; its own waits count its own operations only, and with
-// these in flight beside them they wait for more, not less.)
+// these in flight beside them they wait for more, not less.)  A scalar register that a vector
+// instruction wrote (a readfirstlane of off, of the descriptor) is not read by a vector memory
+// instruction within five wait states; the compiler keeps that distance for its own loads but not
+// into a statement, which therefore keeps it itself: the move to m0 and four more.
 __device__ __forceinline__ u32x4 desc_of(const void *p) {
     const unsigned long long v = (unsigned long long)p;
     u32x4 d;
@@ -330,7 +333,7 @@ __device__ __forceinline__ u32x4 desc_of(const void *p) {
     return d;
 }
 __device__ __forceinline__ void load_lds16(u32x4 d, unsigned lane_off, unsigned off, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(lane_off), "s"(d),
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(lane_off), "s"(d),
                  "s"(__builtin_amdgcn_readfirstlane(off)), "s"(__builtin_amdgcn_readfirstlane(lds))
                  : "m0", "memory");
 }

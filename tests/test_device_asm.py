@@ -43,3 +43,22 @@ __global__ void probe(const void *src, double *out) {
     assert len(loads) == 3
     m0 = [i for i, x in enumerate(lines) if re.match(r"s_mov(k_i32|_b32) m0,", x)]
     assert any(loads[1] < i < loads[2] for i in m0)
+
+
+def test_loads_to_lds_wait_for_scalars_that_a_vector_instruction_wrote(tmp_path):
+    """Five wait states between a readfirstlane and the load that takes its result as the offset."""
+    lines = assembly(tmp_path, """
+__global__ void probe(const void *src, const unsigned *off, double *out) {
+    __shared__ double buf[256];
+    load_lds16(desc_of(src), threadIdx.x * 16u, off[threadIdx.x], lds_off(buf));
+    wait_lds<0>();
+    out[threadIdx.x] = buf[threadIdx.x];
+}""")
+    load = next(i for i, x in enumerate(lines) if x.startswith("buffer_load") and x.endswith("lds"))
+    soffset = lines[load].split(",")[2].split()[0]
+    write = max(i for i, x in enumerate(lines[:load]) if re.match(rf"\S+ {soffset},", x))
+    assert lines[write].startswith("v_readfirstlane_b32")
+    states = 0
+    for x in lines[write + 1:load]:
+        states += int(x.split()[1]) + 1 if x.startswith("s_nop") else 1
+    assert states >= 5
