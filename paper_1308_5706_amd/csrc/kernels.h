@@ -256,12 +256,12 @@ constexpr int pkind_a(int k) { return (k >> 8) & 0x7ff; }
 constexpr int pkind_b(int k) { return k & 0xff; }
 constexpr int kPersistMaxP = 2048;  // largest transform of the executor (P / 8 <= 256 threads)
 
-struct PadArgs {
+struct PadArgs {  // item i: elements 256 i .. 256 i + 255 of the rows x Lp array
     const double2 *flm;
     const double *g;
     const int *rowl;
     double2 *fpad;
-    int L, Lp;
+    int L, Lp, rows;
     size_t s_fpad;
 };
 struct ScalingArgs {

@@ -16,8 +16,8 @@ __global__ void pad_flm_kernel(const double2 *flm, const double *g, const int *r
 hipError_t launch_pad_flm(const double2 *flm, const double *g, const int *rowl, int rows, double2 *fpad, int L, int Lp,
                           size_t s_fpad, int maps, hipStream_t st) {
     if (t_rec)
-        return rec_job(pkind(PS_PAD, 0), (long long)((Lp + 255) / 256) * rows, maps, 256,
-                       PadArgs{flm, g, rowl, fpad, L, Lp, s_fpad});
+        return rec_job(pkind(PS_PAD, 0), ((long long)rows * Lp + 255) / 256, maps, 256,
+                       PadArgs{flm, g, rowl, fpad, L, Lp, rows, s_fpad});
     hipLaunchKernelGGL(pad_flm_kernel, dim3((Lp + 255) / 256, rows, maps), dim3(256), 0, st, flm, g, rowl, fpad, L, Lp,
                        s_fpad);
     return hipGetLastError();
