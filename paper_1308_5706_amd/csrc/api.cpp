@@ -48,6 +48,7 @@ struct Shape {
         size_t s_F = 0;
     } adj[2];
     size_t s_F() const { return std::max(adj[0].s_F, adj[1].s_F); }
+    bool by_size = true;                        // the default: slots by direction, precision and size
     int chunk = 1;                              // maps per batched launch sequence (tunable)
     // the fused alpha and gamma kernels of the prime-factor lengths (tunable): 0 never,
     // 1 where they were measured faster than the two-pass form (fuse_fwd, fuse_adj),
@@ -406,11 +407,15 @@ int tile_set(Plan &P, int R, const Plan::TileSet *&out) {
     return S2DW_OK;
 }
 
+// The synthesis slots of the default shape.
+int default_slots(const Plan &P, int f32) { return wig_adj_slots(P.K, (long)(P.Lp / 64) * P.L, f32); }
+
 // Sets the plan's shape to R slots in the analysis and in both precisions of the synthesis;
 // by_size (the default shape): by the size of the call, and of one map in the synthesis.
 int set_slots(Plan &P, int R, bool by_size = false) {
     const Plan::TileSet *ts = nullptr;
     Shape sh = P.cur;
+    sh.by_size = by_size;
     sh.nfwd = 0;
     int Ropt[3] = {R};
     const int nopt = by_size ? wig_slot_options(P.K, Ropt) : 1;
@@ -420,7 +425,7 @@ int set_slots(Plan &P, int R, bool by_size = false) {
         sh.fwd[sh.nfwd++] = {Ropt[i], ts->fwd, ts->nfwd_plain, ts->nfwd_x};
     }
     for (int f32 = 0; f32 < 2; ++f32) {
-        const int Ra = by_size ? wig_adj_slots(P.K, (long)(P.Lp / 64) * P.L, f32) : R;
+        const int Ra = by_size ? default_slots(P, f32) : R;
         int rc = tile_set(P, Ra, ts);
         if (rc != S2DW_OK) return rc;
         const int group = kAdjWaves * Ra, nblk = (P.L + group - 1) / group;
@@ -2241,11 +2246,14 @@ int s2dw_autotune(const s2dw_params *p, int32_t count, void *stream, int32_t *sl
     hipEventCreate(&e0);
     hipEventCreate(&e1);
     s2dw_params q = *p;
+    // tile shapes by the slots that set_tuning takes: those of the default stand for it
+    const int R0 = default_slots(*P, f32);
+    auto take = [&](int R) { return set_slots(*P, R, R == R0); };
     // seconds per map of a round trip with tile shape R, batch chunk c and fusion form fu
     auto trial = [&](int R, int c, int fu, double &sec) -> int {
         {
             std::lock_guard<std::mutex> lk(g_mu);
-            int r2 = set_slots(*P, R);
+            int r2 = take(R);
             if (r2 != S2DW_OK) return r2;
             P->cur.chunk = c;
             P->cur.fuse = fu;
@@ -2265,7 +2273,8 @@ int s2dw_autotune(const s2dw_params *p, int32_t count, void *stream, int32_t *sl
     };
     int Ropt[3];
     const int nR = wig_slot_options(P->K, Ropt);
-    int bestR = shape_of(*P).adj[f32].R, bestC = cmax, bestF = 1;
+    std::iter_swap(Ropt, std::find(Ropt, Ropt + nR, R0));  // the default first
+    int bestR = R0, bestC = cmax, bestF = 1;
     double best = 1e30;
     for (int i = 0; i < nR && rc == S2DW_OK; ++i) {
         double sec = 0;
@@ -2310,7 +2319,7 @@ int s2dw_autotune(const s2dw_params *p, int32_t count, void *stream, int32_t *sl
     if (rc != S2DW_OK) return rc;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        rc = set_slots(*P, bestR);
+        rc = take(bestR);
         P->cur.chunk = bestC;
         P->cur.fuse = bestF;
     }
@@ -2358,8 +2367,11 @@ int s2dw_set_tuning(const s2dw_params *p, int32_t slots, int32_t chunk, int32_t 
     int Ropt[3];
     const int nR = wig_slot_options(P->K, Ropt);
     if (std::find(Ropt, Ropt + nR, (int)slots) == Ropt + nR) return S2DW_E_ARG;
+    const int f32 = p->precision == S2DW_MIXED ? 1 : 0;
     std::lock_guard<std::mutex> lk(g_mu);
-    rc = set_slots(*P, slots);
+    // the slots that get_tuning reports now leave the shape as it is (the default, or one set through
+    // the other precision); those of the default otherwise bring it back
+    if (slots != P->cur.adj[f32].R) rc = set_slots(*P, slots, slots == default_slots(*P, f32));
     if (rc != S2DW_OK) return rc;
     P->cur.chunk = chunk;
     P->cur.fuse = fuse;

@@ -304,8 +304,9 @@ def synthesis_batched(W: torch.Tensor, Wphi: torch.Tensor | None, L: int, N: int
 
 def autotune(L: int, N: int, lam: float = 2.0, J_min: int = 0, *, count: int = 1, precision: str = "fp64",
              stream=None, grid: str = "mw", reality: bool = True):
-    """Times the compiled Wigner tile shapes and batch chunks for these parameters and keeps
-    the fastest in the library's plan; returns (m' slots per wave, maps per chunk)."""
+    """Times the default Wigner tile shape, the other compiled ones and batch chunks for these
+    parameters and keeps the fastest in the library's plan; returns (m' slots per wave, maps per
+    chunk), the slots as get_tuning reports them."""
     sl, ch = ctypes.c_int32(), ctypes.c_int32()
     _check(lib().s2dw_autotune(ctypes.byref(params(L, N, lam, J_min, precision, grid, reality)), count, _stream(stream),
                                ctypes.byref(sl), ctypes.byref(ch)), "s2dw_autotune")
@@ -383,7 +384,9 @@ FUSE_FORMS = {"two-pass": 0, "default": 1, "fused": 2}
 
 def get_tuning(L: int, N: int, lam: float = 2.0, J_min: int = 0, *, precision: str = "fp64", grid: str = "mw",
                reality: bool = True):
-    """The plan's tuning: (m' slots per wave, maps per chunk, alpha/gamma form 0..2)."""
+    """The plan's tuning: (m' slots per wave, maps per chunk, alpha/gamma form 0..2).  The default
+    tile shape, whose slots follow direction, precision and size, is reported as the slots of its
+    synthesis in this precision."""
     sl, ch, fu = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
     _check(lib().s2dw_get_tuning(ctypes.byref(params(L, N, lam, J_min, precision, grid, reality)), ctypes.byref(sl),
                                  ctypes.byref(ch), ctypes.byref(fu)), "s2dw_get_tuning")
@@ -392,7 +395,9 @@ def get_tuning(L: int, N: int, lam: float = 2.0, J_min: int = 0, *, precision: s
 
 def set_tuning(L: int, N: int, lam: float = 2.0, J_min: int = 0, *, slots: int, chunk: int, fuse,
                precision: str = "fp64", grid: str = "mw", reality: bool = True) -> None:
-    """Applies a tuning (e.g. one autotune found before); fuse is 0..2 or a FUSE_FORMS name."""
+    """Applies a tuning (e.g. one autotune found before); fuse is 0..2 or a FUSE_FORMS name.  What
+    get_tuning reports changes nothing; the slots of the default bring the default tile shape back,
+    others go for both directions and precisions."""
     fu = FUSE_FORMS[fuse] if isinstance(fuse, str) else int(fuse)
     _check(lib().s2dw_set_tuning(ctypes.byref(params(L, N, lam, J_min, precision, grid, reality)), slots, chunk, fu),
            "s2dw_set_tuning")
