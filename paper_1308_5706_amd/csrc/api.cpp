@@ -1173,13 +1173,33 @@ struct RefGroup {
     int kind, size, nwg;
     ScaleRefs refs;
 };
-void add_ref(std::vector<RefGroup> &v, int kind, int size, int nwg, int Lj, size_t in_off, size_t out_off, const void *hh,
-             int B = 0, int nblk = 0) {
-    if (v.empty() || v.back().kind != kind || v.back().size != size) v.push_back(RefGroup{kind, size, 0, {}});
-    RefGroup &g = v.back();
-    g.refs.s[g.refs.n++] = ScaleRef{g.nwg, Lj, (long long)in_off, (long long)out_off, hh, B, nblk};
-    g.nwg += nwg;
-}
+// The scales of one stage of a call, each with its number of workgroups, and the launches they
+// make: runs of one kind and size, taken by next() in order.  Held in place: a call on a plan
+// that exists takes nothing from the heap, which could fail with an exception at the C entry.
+struct RefList {
+    int n = 0, at = 0;
+    struct {
+        int kind, size, nwg;
+    } of[kMaxScales];
+    ScaleRef ref[kMaxScales];
+
+    void add(int kind, int size, int nwg, int Lj, size_t in_off, size_t out_off, const void *hh, int B = 0, int nblk = 0) {
+        of[n] = {kind, size, nwg};
+        ref[n++] = ScaleRef{0, Lj, (long long)in_off, (long long)out_off, hh, B, nblk};
+    }
+    bool next(RefGroup &g) {
+        if (at >= n) return false;
+        g.kind = of[at].kind;
+        g.size = of[at].size;
+        g.nwg = g.refs.n = 0;
+        for (; at < n && of[at].kind == g.kind && of[at].size == g.size; ++at) {
+            ref[at].first = g.nwg;
+            g.refs.s[g.refs.n++] = ref[at];
+            g.nwg += of[at].nwg;
+        }
+        return true;
+    }
+};
 
 // Coarse scales of real signals take the fused alpha and gamma passes (the analysis one
 // in both precisions: it computes in FP64 and reads and writes Ub and W in the plan's
@@ -1241,17 +1261,17 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     const int wmaps = cx ? maps / 2 : maps;
     const bool side = side_by_side(P, w, maps);
     const size_t s_Ub = side ? P.s_Ubs : P.s_Ub;
-    std::vector<RefGroup> direct, fused;  // scales whose alpha and gamma sums follow the loop
+    RefList direct, fused;  // scales whose alpha and gamma sums follow the loop
     StageArgs sb{};                       // the arguments all scales share (side by side)
     if (side) {
         const bool dh = P.grid == S2DW_GRID_DH;
         const Plan::GridTab &gtab = P.gt[L];
-        std::vector<RefGroup> beta;
+        RefList beta;
         for (int j = 0; j < P.S; ++j) {
             const int Lj = P.sc.Lj[j];
             if (Lj == 0) continue;
             const bool pair = !dh && pow2_at_least(2 * Lj + 2 * L - 3) <= P.PA[j];
-            add_ref(beta, pair ? 1 : 0, P.PA[j], N * (pair ? (Lj + 1) / 2 : Lj), Lj, P.sc.off[j], P.uboff[j],
+            beta.add(pair ? 1 : 0, P.PA[j], N * (pair ? (Lj + 1) / 2 : Lj), Lj, P.sc.off[j], P.uboff[j],
                     f32 ? (const void *)P.hAf[j] : P.hA[j]);
         }
         sb.f32 = f32;
@@ -1265,7 +1285,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
         sb.nb = P.nb;
         sb.N = N;
         sb.Nh = P.Nh;
-        for (const RefGroup &g : beta) {
+        for (RefGroup g; beta.next(g);) {
             sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
             Stage sg("beta_fwd", st, g.refs.n);
             S2DW_CHECK_HIP(g.kind ? launch_beta_fwd_pair(sb, g.size, maps, st, &g.refs, g.nwg)
@@ -1335,7 +1355,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
         }
         if (direct_alpha_gamma(P.Nh, P.ng, Lj, cx)) {
             if (side) {
-                add_ref(direct, 0, 0, 0, Lj, P.uboff[j], P.woff[j], nullptr);
+                direct.add(0, 0, 0, Lj, P.uboff[j], P.woff[j], nullptr);
                 continue;
             }
             AlphaGammaArgs d{};
@@ -1374,7 +1394,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             const int nwg = 8 * ((b.nb + 7) / 8);
             const void *hh = f32 ? (const void *)P.hBf[j] : P.hB[j];
             if (side) {
-                add_ref(fused, 0, P.PB[j], nwg, Lj, P.uboff[j], P.woff[j], hh);
+                fused.add(0, P.PB[j], nwg, Lj, P.uboff[j], P.woff[j], hh);
                 continue;
             }
             StageArgs d = b;
@@ -1394,7 +1414,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             const int nwg = 8 * ((b.nb + 7) / 8);
             const void *hh = f32 ? (const void *)P.hBbf[j] : P.hBb[j];
             if (side) {
-                add_ref(fused, 1, P.PBb[j], nwg, Lj, P.uboff[j], P.woff[j], hh, P.Bb[j], P.nblkb[j]);
+                fused.add(1, P.PBb[j], nwg, Lj, P.uboff[j], P.woff[j], hh, P.Bb[j], P.nblkb[j]);
                 continue;
             }
             StageArgs d = b;
@@ -1454,13 +1474,13 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             else S2DW_CHECK_HIP(launch_gamma_fwd(g, maps, st));
         }
     }
-    for (const RefGroup &g : fused) {
+    for (RefGroup g; fused.next(g);) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
         Stage sg("alpha_gamma_fwd", st, g.refs.n);
         S2DW_CHECK_HIP(g.kind ? launch_fused_blk<true>(sb, g.refs, g.nwg, g.size, maps, st)
                               : fused_fwd(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }
-    for (const RefGroup &g : direct) {
+    for (RefGroup g; direct.next(g);) {
         AlphaGammaArgs d{};
         d.in = w.Ub;
         d.wout = W;
@@ -1494,7 +1514,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
     const size_t s_Ub = side ? P.s_Ubs : P.s_Ub;
     StageArgs sb{};
     GammaAlphaArgs sd{};
-    std::vector<RefGroup> direct, fusedg, betadh;  // scales whose sums follow the loop
+    RefList direct, fusedg, betadh;  // scales whose sums follow the loop
     for (int j = 0; j < P.S; ++j) {
         const int Lj = P.sc.Lj[j], Lg = P.Lg[j], M = 2 * Lg - 1;
         if (Lj == 0) continue;
@@ -1543,7 +1563,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             d.eph = f32 ? (const void *)gtab.ephf : gtab.eph;
             d.tw = f32 ? (const void *)P.twPf[size] : P.twP[size];
             if (side) {
-                add_ref(fusedg, blk ? 1 : 0, size, nwg, Lj, P.woff[j], uo, hh, B, nblk);
+                fusedg.add(blk ? 1 : 0, size, nwg, Lj, P.woff[j], uo, hh, B, nblk);
                 sb = d;
             } else {
                 const ScaleRefs refs{1, {{0, Lj, 0, 0, hh, B, nblk}}};
@@ -1586,7 +1606,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             d.scale = qscale;
             d.f32 = f32;
             if (side) {
-                add_ref(direct, 0, 0, 0, Lj, P.woff[j], uo, nullptr);
+                direct.add(0, 0, 0, Lj, P.woff[j], uo, nullptr);
                 d.Lj = std::max(d.Lj, sd.Lj);
                 sd = d;
             } else {
@@ -1636,7 +1656,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             S2DW_CHECK_HIP(launch_alpha_adj_fft(c, P.PB[j], maps, st));
         }
         if (side && dh)
-            add_ref(betadh, 0, P.PE[j], P.K * Lj, Lj, uo, P.sc.off[j], f32 ? (const void *)P.hEf[j] : P.hE[j]);
+            betadh.add(0, P.PE[j], P.K * Lj, Lj, uo, P.sc.off[j], f32 ? (const void *)P.hEf[j] : P.hE[j]);
         if (merged) continue;
         StageArgs v = c;
         v.in = w.Ub;
@@ -1665,17 +1685,17 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
             S2DW_CHECK_HIP(launch_beta_adj_fft(v, gtab.PD, maps, st));
         }
     }
-    for (const RefGroup &g : fusedg) {
+    for (RefGroup g; fusedg.next(g);) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
         Stage sg("gamma_alpha_adj", st, g.refs.n);
         S2DW_CHECK_HIP(g.kind ? launch_fused_blk<false>(sb, g.refs, g.nwg, g.size, maps, st)
                               : fused_adj(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }
-    for (const RefGroup &g : direct) {
+    for (RefGroup g; direct.next(g);) {
         Stage sg("gamma_alpha_adj", st, g.refs.n);
         S2DW_CHECK_HIP(launch_gamma_alpha_adj(sd, maps, st, &g.refs));
     }
-    if (!betadh.empty() || (side && P.sns > 0) || P.mj0 >= 0) {
+    if (betadh.n > 0 || (side && P.sns > 0) || P.mj0 >= 0) {
         const bool dh = P.grid == S2DW_GRID_DH;
         const Plan::GridTab &gtab = P.gt[L];
         StageArgs v{};
@@ -1698,7 +1718,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
         v.K = P.K;
         for (int k = 0; k < P.K; ++k) v.nk[k] = P.ht.nk[k];
         v.eta_imag = P.ht.eta_imag ? 1 : 0;
-        for (const RefGroup &g : betadh) {
+        for (RefGroup g; betadh.next(g);) {
             v.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
             Stage sg("beta_adj", st, g.refs.n);
             S2DW_CHECK_HIP(launch_beta_adj_dh(v, g.size, maps, st, &g.refs, g.nwg));
