@@ -2061,11 +2061,13 @@ int run_persistent(int dir, const s2dw_group *groups, int32_t ngroups, int32_t *
 
 namespace s2dw {
 
-// The padded f_lm takes the Wigner stage's table rows instead of L rows: at most 8 rows per
-// segment (kMaxSegs at most, two segments per scale) more, and those read ahead.  The size a call
-// may take is still that of L rows within S2DW_NOALLOC_SCRATCH_BYTES, which keeps Lp below 768, and
-// 512 for the two maps of a complex signal: these bytes hold the extra rows.
+// The padded f_lm takes the Wigner stage's table rows instead of L rows: up to 7 more at the ends of
+// each segment and those read ahead.  The calls that s2dw_analysis_noalloc takes are still those whose
+// arrays with L rows fit S2DW_NOALLOC_SCRATCH_BYTES, and these bytes hold the rows beyond: over L, N,
+// J_min, the grids and lambda from 1.01 to 5000, the largest such call takes 2.7 MB of them (complex,
+// L = 389, N = 2, lambda = 1.2, 25 segments).  The call checks the arrays that it lays out all the same.
 constexpr size_t kScratchRows = 8ull << 20;
+constexpr size_t kScratchBytes = S2DW_NOALLOC_SCRATCH_BYTES + kScratchRows;
 
 // Fixed device scratch of s2dw_analysis_noalloc (the stage workspaces of one call): one copy
 // per GPU, held until the process ends.  In host code the name is only a stand-in for the
@@ -2073,7 +2075,7 @@ constexpr size_t kScratchRows = 8ull << 20;
 // File-scope array with external linkage: a `static` one keeps a local binding in the
 // device code object, outside its dynamic symbol table, and the runtime cannot resolve
 // it by name.
-__device__ __align__(256) double2 scratch[(S2DW_NOALLOC_SCRATCH_BYTES + kScratchRows) / sizeof(double2)];
+__device__ __align__(256) double2 scratch[kScratchBytes / sizeof(double2)];
 
 namespace {
 
@@ -2441,6 +2443,8 @@ int s2dw_analysis_noalloc(const s2dw_params *p, const double *flm, void *W, doub
     const int per = cx ? 2 : 1;  // real maps of the signal
     const size_t per_map = (size_t)P->L * P->Lp + P->s_U + P->s_Ub + P->s_Y;  // complex elements
     if ((size_t)per * per_map * sizeof(double2) > S2DW_NOALLOC_SCRATCH_BYTES) return S2DW_E_UNSUPPORTED;
+    const size_t laid_out = P->s_fpad + P->s_U + P->s_Ub + P->s_Y;
+    if ((size_t)per * laid_out * sizeof(double2) > kScratchBytes) return S2DW_E_UNSUPPORTED;
     double2 *base = nullptr;
     rc = scratch_of_current_device(base);
     if (rc != S2DW_OK) return rc;
