@@ -448,10 +448,25 @@ Shape shape_of(Plan &P) {
 // 14.36: beyond it a scale fills the chip by itself and the memory is not worth it.
 constexpr size_t kSideBytes = (size_t)512 << 20;
 
+// Maps whose Ub arrays of every scale go side by side: as many as fit kSideBytes (16 bytes an element
+// in both precisions, as the workspace that they share has them).
+int side_maps(const Plan &P) {
+    return P.s_Ubs ? (int)std::min<size_t>(kSideBytes / (P.s_Ubs * sizeof(double2)), 1024) : 0;
+}
+
+// Elements of the beta-stage workspace for `maps` maps, and of all of a stream's arrays for them.
+size_t ub_elements(const Plan &P, int maps) {
+    return std::max((size_t)maps * P.s_Ub, (size_t)std::min(maps, side_maps(P)) * P.s_Ubs);
+}
+size_t work_elements(const Plan &P, const Shape &sh, int maps) {
+    return (size_t)maps * (P.s_fpad + P.s_U + P.s_Y + sh.s_F()) + ub_elements(P, maps);
+}
+
 // Default maps per batched launch sequence: as many as fit 8 GiB of workspace, at most 64.
 int default_chunk(const Plan &P) {
-    const double per_map = 16.0 * (double)(P.s_fpad + P.s_U + P.s_Ub + P.s_Y + P.cur.s_F());
-    return (int)std::max(1.0, std::min(64.0, std::floor(8.0 * (1ull << 30) / per_map)));
+    int c = 64;
+    while (c > 1 && work_elements(P, P.cur, c) * sizeof(double2) > (size_t)8 << 30) --c;
+    return c;
 }
 
 typedef long double ld;
@@ -1029,16 +1044,6 @@ bool walloc(Work &w, T *&p, size_t count) {
     w.bytes += count * sizeof(T);
     p = (T *)q;
     return true;
-}
-
-// Maps whose Ub arrays of every scale go side by side: as many as fit kSideBytes.
-int side_maps(const Plan &P) {
-    return P.s_Ubs ? (int)std::min<size_t>(kSideBytes / (P.s_Ubs * sizeof(double2)), 1024) : 0;
-}
-
-// Elements of the beta-stage workspace for `maps` maps.
-size_t ub_elements(const Plan &P, int maps) {
-    return std::max((size_t)maps * P.s_Ub, (size_t)std::min(maps, side_maps(P)) * P.s_Ubs);
 }
 
 // The workspace of `stream` for a batch of `maps` maps with per-map partial sums of s_F
@@ -2408,10 +2413,9 @@ int s2dw_workspace_bytes(const s2dw_params *p, int32_t count, uint64_t *bytes) {
     rc = get_plan(kWavelet, p->L, p->N, p->lambda, p->J_min, P, p->precision == S2DW_MIXED, p->grid);
     if (rc != S2DW_OK) return rc;
     const Shape sh = shape_of(*P);
-    const uint64_t per_map = 16ull * (P->s_fpad + P->s_U + P->s_Y + sh.s_F());
     const int per = p->reality == 0 ? 2 : 1;  // real maps per signal
     const int maps = per * std::min<int>(count, std::max(sh.chunk / per, 1));
-    *bytes = per_map * maps + 16ull * ub_elements(*P, maps);
+    *bytes = work_elements(*P, sh, maps) * sizeof(double2);
     return S2DW_OK;
 }
 
