@@ -20,3 +20,27 @@ def test_default_chunk_fits_its_workspace(L, N, J_min, grid):
     one = s2dw.workspace_bytes(L, N, 2.0, J_min, count=1, grid=grid)
     assert chunk == 64 or (chunk + 2) * one > 8 << 30  # and is not smaller than it need be
     s2dw.release_caches()
+
+
+# 512 MiB hold 21 maps of L = 256, N = 8 (a complex signal is two maps), 13 on the Driscoll-Healy grid
+# of L = 230 and 39 of L = 536, N = 1: a batch on either side of the line
+@pytest.mark.parametrize("L,N,J_min,grid,reality,below,beyond", [
+    (256, 8, 0, "mw", True, 20, 24), (230, 8, 0, "dh", True, 13, 18), (256, 8, 0, "mw", False, 10, 12),
+    (536, 1, 3, "mw", True, 38, 41)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_maps_of_a_batch_equal_single_calls_across_the_line(L, N, J_min, grid, reality, below, beyond, precision):
+    print(f"L={L} N={N} {grid} reality={reality} {precision}", flush=True)
+    A = (L, N, 2.0, J_min)
+    kw = dict(precision=precision, grid=grid, reality=reality)
+    f = torch.stack([torch.as_tensor((random_flm if reality else random_flm_complex)(L, i), device="cuda")
+                     for i in range(beyond)])
+    for count in (below, beyond):
+        W, Wp = s2dw.analysis_batched(f[:count], *A, **kw)
+        back = s2dw.synthesis_batched(W, Wp, *A, **kw)
+        for i in (0, count // 2, count - 1):
+            W1, Wp1 = s2dw.analysis(f[i], *A, **kw)
+            assert torch.equal(W[i], W1) and torch.equal(Wp[i], Wp1), (count, i)
+            assert torch.equal(back[i], s2dw.synthesis(W1, Wp1, *A, **kw)), (count, i)
+        del W, Wp, back
+    s2dw.release_caches()
+    torch.cuda.empty_cache()
