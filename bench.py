@@ -552,7 +552,7 @@ def main():
 
     def per_launch(stages):
         return {k: {"ms_per_launch": v[0] / v[1], "launches_per_step": v[1] / args.steps,
-                    "ms_per_step": v[0] / args.steps} for k, v in stages.items()}
+                    "ms_per_step": v[0] / args.steps} for k, v in stages.items() if v[1] > 0}
 
     # Per-stage breakdown from an untimed pass with every stage timed; it picks the kernel
     # with the largest device time per step (one stage = one kernel launch per scale, or per

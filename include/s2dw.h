@@ -329,9 +329,9 @@ int s2dw_wavelet_tables(const s2dw_params *p, double *kappa, double *phi, double
  * gamma_fwd, alpha_gamma_fwd (analysis; the last is the fused alpha and gamma pass of
  * real signals), gamma_adj, gamma_alpha_adj (its synthesis counterpart), alpha_adj,
  * beta_adj, wigner_adj, syn_final (synthesis), scaling, steer.  A launch that takes
- * several scales counts one pass for each of them.  While stages are timed, the alpha and
- * gamma sums of scales on grids of band-limit below 64 run as separate passes (with the
- * same results), so that each has a time.
+ * several scales counts one pass for each of them.  With a fused alpha and gamma pass at the
+ * chirp lengths the separate passes that it takes the place of are listed too, with the passes
+ * they made by themselves (0, in 0 ms, where every scale went through fused ones).
  */
 typedef struct s2dw_stage_time {
     char name[24];

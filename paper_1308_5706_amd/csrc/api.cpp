@@ -203,16 +203,26 @@ thread_local bool t_no_events = false;
 thread_local Recorder *t_rec = nullptr;  // work-list recording (persistent executor), kernels.h
 namespace {
 
+// The separate passes that the fused alpha and gamma kernels take the place of.
+struct StageParts {
+    const char *name[2];
+};
+constexpr StageParts kFwdParts{{"alpha_fwd", "gamma_fwd"}}, kAdjParts{{"gamma_adj", "alpha_adj"}};
+
 // Records events around one launch when timing is on; passes: the stage's passes that the
-// launch makes (one per scale it takes).
+// launch makes (one per scale it takes); parts: stages that are listed too, with the passes they
+// make by themselves (none, if every scale goes this way).
 struct Stage {
     hipStream_t st;
     hipEvent_t a = nullptr;
     const char *name;
     int passes;
-    Stage(const char *n, hipStream_t s, int k = 1) : st(s), name(n), passes(k) {
+    Stage(const char *n, hipStream_t s, int k = 1, const StageParts *parts = nullptr) : st(s), name(n), passes(k) {
         if (!g_prof.on || t_no_events) return;
         std::lock_guard<std::mutex> lk(g_prof.mu);
+        if (parts)
+            for (const char *q : parts->name)
+                if (g_prof.only.empty() || g_prof.only.count(q)) g_prof.totals[q];
         if (!g_prof.only.empty() && !g_prof.only.count(n)) return;
         a = prof_event();
         if (a) hipEventRecord(a, st);
@@ -1143,9 +1153,6 @@ bool fuse_adj(const Plan &P, const Shape &sh, int f32, int T) {
 bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
     const int T = 2 * P.Lg[j] - 1;
     if (t_rec || pfa_length(T) || !fused_fft(P.PB[j], T, P.Nh, cx)) return false;
-    // while stages are timed, the alpha and gamma sums of the smallest maps (in no size blocked, so
-    // with the same results) stay apart, each with a time of its own
-    if (g_prof.on && !t_no_events && P.Lg[j] < 64) return false;
     return P.nblkb[j] <= 1 || !f32;
 }
 
@@ -1411,7 +1418,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             d.G = P.ng;
             d.tw = f32 ? (const void *)P.twPf[P.PB[j]] : P.twP[P.PB[j]];
             d.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
-            Stage sg("alpha_gamma_fwd", st);
+            Stage sg("alpha_gamma_fwd", st, 1, &kFwdParts);
             S2DW_CHECK_HIP(fused_fwd(d, ScaleRefs{1, {{0, Lj, 0, 0, hh, 0, 0}}}, nwg, P.PB[j], maps, cx, st));
             continue;
         }
@@ -1432,7 +1439,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
             d.tw = f32 ? (const void *)P.twPf[P.PBb[j]] : P.twP[P.PBb[j]];
             d.csq = f32 ? (const void *)gtab.csqf : gtab.csq;
             d.eph = f32 ? (const void *)gtab.ephf : gtab.eph;
-            Stage sg("alpha_gamma_fwd", st);
+            Stage sg("alpha_gamma_fwd", st, 1, &kFwdParts);
             S2DW_CHECK_HIP(launch_fused_blk<true>(d, ScaleRefs{1, {{0, Lj, 0, 0, hh, P.Bb[j], P.nblkb[j]}}}, nwg, P.PBb[j],
                                                   maps, st));
             continue;
@@ -1481,7 +1488,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     }
     for (RefGroup g; fused.next(g);) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
-        Stage sg("alpha_gamma_fwd", st, g.refs.n);
+        Stage sg("alpha_gamma_fwd", st, g.refs.n, &kFwdParts);
         S2DW_CHECK_HIP(g.kind ? launch_fused_blk<true>(sb, g.refs, g.nwg, g.size, maps, st)
                               : fused_fwd(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }
@@ -1572,7 +1579,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
                 sb = d;
             } else {
                 const ScaleRefs refs{1, {{0, Lj, 0, 0, hh, B, nblk}}};
-                Stage sg("gamma_alpha_adj", st);
+                Stage sg("gamma_alpha_adj", st, 1, &kAdjParts);
                 S2DW_CHECK_HIP(blk ? launch_fused_blk<false>(d, refs, nwg, size, maps, st)
                                    : fused_adj(d, refs, nwg, size, maps, cx, st));
             }
@@ -1692,7 +1699,7 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
     }
     for (RefGroup g; fusedg.next(g);) {
         sb.tw = f32 ? (const void *)P.twPf[g.size] : P.twP[g.size];
-        Stage sg("gamma_alpha_adj", st, g.refs.n);
+        Stage sg("gamma_alpha_adj", st, g.refs.n, &kAdjParts);
         S2DW_CHECK_HIP(g.kind ? launch_fused_blk<false>(sb, g.refs, g.nwg, g.size, maps, st)
                               : fused_adj(sb, g.refs, g.nwg, g.size, maps, cx, st));
     }

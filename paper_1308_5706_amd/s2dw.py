@@ -500,7 +500,8 @@ def profile_stages(names=None) -> None:
 
 
 def profile_read() -> dict:
-    """{stage: (total_ms, passes)} since the last clear (waits for the recorded events)."""
+    """{stage: (total_ms, passes)} since the last clear (waits for the recorded events).  A stage may
+    be listed with no passes: one that fused passes took the place of in every scale."""
     buf = (StageTime * 64)()
     n = ctypes.c_int32()
     _check(lib().s2dw_profile_read(buf, 64, ctypes.byref(n)), "s2dw_profile_read")
