@@ -12,12 +12,32 @@ static hipError_t launch_fwd_k(const WigFwdArgs &a, int ntiles, int maps, hipStr
     return hipGetLastError();
 }
 
+// More workgroups than CUs: the FULL form of the one-slot synthesis where it has one (FP64: up to two
+// orders, whose registers allow it; FP32: from seven on, where the ordinary form has not four waves per
+// SIMD already).  Measured, synthesis stage with the final sum, us, ordinary against FULL: 16 maps of L = 128,
+// N = 1 65 against 54, 64 maps 216 against 167; 8 maps of L = 256, N = 4 155 against 136; mixed, 8 maps of
+// L = 200, N = 16 167 against 131; one map of it 83 against 84, 16 maps of L = 100, N = 4 (416 workgroups)
+// 49 against 50.
+template <int K, int R, typename VT>
+constexpr bool has_full() { return R == 1 && (sizeof(VT) == 8 ? K <= 2 : K >= 7); }
+
+template <int K, int R, typename VT>
+static hipError_t launch_adj_t(const WigAdjArgs &a, int ntiles, int maps, hipStream_t st) {
+    const dim3 grid(ntiles, maps), nt(kAdjThreads);
+    if constexpr (has_full<K, R, VT>()) {
+        if ((long)ntiles * maps > 256) {
+            hipLaunchKernelGGL((wig_adj_full_kernel<K, VT>), grid, nt, 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((wig_adj_kernel<K, R, VT>), grid, nt, 0, st, a);
+    return hipGetLastError();
+}
+
 template <int K, int R>
 static hipError_t launch_adj_k(const WigAdjArgs &a, int ntiles, int maps, hipStream_t st) {
     if (ntiles <= 0) return hipSuccess;
-    if (a.f32) hipLaunchKernelGGL((wig_adj_kernel<K, R, float>), dim3(ntiles, maps), dim3(kAdjThreads), 0, st, a);
-    else hipLaunchKernelGGL((wig_adj_kernel<K, R, double>), dim3(ntiles, maps), dim3(kAdjThreads), 0, st, a);
-    return hipGetLastError();
+    return a.f32 ? launch_adj_t<K, R, float>(a, ntiles, maps, st) : launch_adj_t<K, R, double>(a, ntiles, maps, st);
 }
 
 // m' slots per wave.  The accumulators (analysis) or quadrature values (synthesis) take 16 R K

@@ -525,10 +525,12 @@ struct WigRows {
 // Table blocks of the analysis kernel's values held in LDS: the one in use, the next, and those on
 // their way.  A block is requested NS - 2 blocks before it is needed; measured at L = 1024, N = 8,
 // a load takes about a block of two resident waves per SIMD, and with one slot and order per
-// wave (small L: few waves, short blocks) several.  Two workgroups share a CU's LDS at the
-// shapes that are picked for large L.
+// wave (small L: few waves, short blocks) several.  No more of them than let two workgroups share a
+// CU's LDS: with six blocks for one slot one was left, and launches of more workgroups than CUs
+// waited (us, six against five: 64 maps of L = 48, N = 4 35 against 27; one map of L = 421, N = 6 62
+// against 49; of L = 256, N = 8 39 with either).
 template <int K, int R>
-constexpr int wig_fwd_slots() { return K >= 5 ? 4 : (R == 1 ? 6 : (R == 2 ? 4 : 3)); }
+constexpr int wig_fwd_slots() { return K >= 5 ? 4 : (R == 1 ? 5 : (R == 2 ? 4 : 3)); }
 
 template <int K, int R>
 struct alignas(16) WigFwdLds {
@@ -704,22 +706,30 @@ constexpr int adj_slice() {
                                                                      : (int)sizeof(WigState<R>) / (2 * (int)sizeof(VT));
 }
 
-template <int K, int R, typename VT, int AW>
+// FULL: the form for four waves per SIMD (wig_adj_full_kernel): in FP64 one window instead of two, so that
+// the LDS of two workgroups fits a CU, and in both types the window sums taken at once.
+template <int K, int R, typename VT, int AW, bool FULL = false>
 struct alignas(16) WigAdjLds {
-    VT win[2][AW][adj_slice<R, VT>()][2];  // two windows of eight steps
+    static constexpr bool ONE = FULL && sizeof(VT) == 8;
+    static constexpr int SL = ONE ? 8 * 64 : adj_slice<R, VT>();                       // slice of a wave
+    static constexpr int ST = ONE ? (int)sizeof(WigState<R>) / (2 * (int)sizeof(VT)) : 0;  // its state, if apart
+    VT win[((ONE ? 1 : 2) * SL + ST) * AW][2];  // the windows of eight steps (then the states)
     WigSlots<K, R, VT, 2> s[AW];
 };
 
 // Tile bx of map by; thread tid of AW 64 (AW waves, each with R m' slots).
-template <int K, int R, bool XN, typename VT, int AW = kAdjWaves>
-__device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R, VT, AW> *lds, int bx, int by,
+template <int K, int R, bool XN, typename VT, int AW = kAdjWaves, bool FULL = false>
+__device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R, VT, AW, FULL> *lds, int bx, int by,
                                              int tid) {
+    using Lds = WigAdjLds<K, R, VT, AW, FULL>;
+    constexpr bool ONE = Lds::ONE;
     // VT = double (FP64 path) or float (mixed precision: the m'-sum, its products and its
     // accumulation in FP32; the Delta recursion stays FP64)
     using VC = typename std::conditional<sizeof(VT) == 8, double2, float2>::type;
     typedef VT vc2 __attribute__((ext_vector_type(2)));
-    constexpr int SL = adj_slice<R, VT>();
-    constexpr int PF = sizeof(VT) == 8 && K * R >= 8 ? 4 : 8;  // steps pt is loaded ahead
+    constexpr int SL = Lds::SL;
+    // steps pt is loaded ahead (fewer where the registers are short)
+    constexpr int PF = (sizeof(VT) == 8 ? K * R >= 8 : K == 6 || (FULL && K > 6)) ? 4 : 8;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
     const int4 t = uniform_tile(a.tiles + bx);
@@ -728,7 +738,9 @@ __device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R
     const int mpb = t.y + wave * R;
     const int wg_start = max(t.x, t.y);                 // smallest l with a non-zero term in the group
     const int lhead = min(L - 1, max(t.x + 63, t.y + AW * R - 1));  // of every wave of the workgroup
-    vc2 *const win = (vc2 *)&lds->win[0][0][0][0];
+    vc2 *const win = (vc2 *)&lds->win[0][0];
+    // the saved state of the wave: in its slice of window b, which is free then, or apart
+    auto state = [&](int b) { return (WigState<R> *)(win + (ONE ? AW * SL + wave * Lds::ST : (b * AW + wave) * SL)); };
 
     WigRows<K, R, XN, VT, 2> w;
     w.init(a.seed, a.seedm, a.seede, L, Lp, a.kstride, a.ustride, m, mpb, lane, &lds->s[wave]);
@@ -785,9 +797,10 @@ __device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R
     // does not depend on timing), is taken during the next block, one slice per step, so that
     // its LDS reads run beside the multiply-adds (summed at once after the barrier, all waves
     // read together and nothing else ran).  Not with four slots of two orders in FP64, whose
-    // registers are all taken.  A wave sums the rows wave, wave + AW, ..; the
-    // window's block starts at plb, its rows pl0 <= l - plb < pl1 are stored.
-    constexpr bool PIPE = !(sizeof(VT) == 8 && K == 2 && R == 4);
+    // registers are all taken, nor in the FULL form, where the CU's other workgroup runs beside it.
+    // A wave sums the rows wave, wave + AW, ..; the window's block starts at plb, its rows
+    // pl0 <= l - plb < pl1 are stored.
+    constexpr bool PIPE = !FULL && !(sizeof(VT) == 8 && K == 2 && R == 4);
     int plb = 0, pl0 = 0, pl1 = 0;
     vc2 part[3];
     auto sum_store = [&](int li, vc2 v) {
@@ -814,7 +827,7 @@ __device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R
     static_assert(AW == 4 || AW == 8, "a wave sums 8 / AW rows of AW slices");
     auto sum_slot = [&](const vc2 *w0, int S) { return w0[(S % AW) * SL + (wave + AW * (S / AW)) * 64 + lane]; };
     auto sum_now = [&] {
-        const vc2 *w0 = win + (buf ^ 1) * (AW * SL);
+        const vc2 *w0 = win + (ONE ? 0 : buf ^ 1) * (AW * SL);
         eight([&](auto s_c) { sum_add(s_c, sum_slot(w0, decltype(s_c)::value)); });
         pl1 = pl0;
     };
@@ -829,8 +842,8 @@ __device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R
             // the state goes to the wave's slice of the other window, once its sums are read; the
             // next block restores it before it writes there
             if constexpr (PIPE) sum_now();
-            lds_barrier();
-            w.save((WigState<R> *)(win + ((buf ^ 1) * AW + wave) * SL));
+            if constexpr (!ONE) lds_barrier();
+            w.save(state(buf ^ 1));
         }
         vc2 *const slice = win + (buf * AW + wave) * SL + lane;
         const vc2 *const w0 = win + (buf ^ 1) * (AW * SL);
@@ -863,13 +876,14 @@ __device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R
         });
         if (!HEAD || !last || !(sg.s1 & 7)) w.renorm();
         w.advance();
-        // one barrier per window: the window written next was read before it
+        // one barrier per window: the window written next was read before it (two with one window)
         lds_barrier();
         plb = lb;
         pl0 = max(lo - lb, 0);
         pl1 = min(sg.s1 - lb, 8);
-        buf ^= 1;
+        if constexpr (!ONE) buf ^= 1;
         if constexpr (!PIPE) sum_now();
+        if constexpr (ONE) lds_barrier();  // read before the next block writes it
         ++blk;
         lb = last ? sg.s1 & ~7 : lb + 8;
         return last;
@@ -882,7 +896,7 @@ __device__ __forceinline__ void wig_adj_body(const WigAdjArgs &a, WigAdjLds<K, R
             while (!last && !(HEAD && lb > lhead));
             if (last) {
                 if (sgn.s1 == 0) return true;
-                if (!HEAD && (sg.s1 & 7)) w.restore((const WigState<R> *)(win + (buf * AW + wave) * SL));
+                if (!HEAD && (sg.s1 & 7)) w.restore(state(buf));
                 lo = sg.s1;
                 sg = sgn;
                 sgn = seg_of(a.segs, ++si + 1);
@@ -917,15 +931,26 @@ __global__ void __launch_bounds__(256, 2) wig_fwd_kernel(const WigFwdArgs a) {
 }
 
 // Waves per SIMD of the synthesis kernel: the LDS of two workgroups of FP32 sums fits a CU, and so
-// do their registers (128) up to four values per wave.
+// do their registers (128) up to four values per wave, six in one slot.
 template <int K, int R, typename VT>
-constexpr int wig_adj_min_waves() { return sizeof(VT) == 4 && K * R <= 4 ? 4 : 2; }
+constexpr int wig_adj_min_waves() { return sizeof(VT) == 4 && (K * R <= 4 || (R == 1 && K <= 6)) ? 4 : 2; }
 
 template <int K, int R, typename VT>
 __global__ void __launch_bounds__(kAdjThreads, (wig_adj_min_waves<K, R, VT>())) wig_adj_kernel(const WigAdjArgs a) {
     __shared__ WigAdjLds<K, R, VT, kAdjWaves> lds;
     if ((int)blockIdx.x < a.nplain) wig_adj_body<K, R, false, VT>(a, &lds, blockIdx.x, blockIdx.y, threadIdx.x);
     else wig_adj_body<K, R, true, VT>(a, &lds, blockIdx.x, blockIdx.y, threadIdx.x);
+}
+
+// One slot per wave, FULL form: four waves per SIMD where the kernel above has two (in FP64 its two
+// windows fill a CU's LDS, in FP32 with seven and eight orders its registers).  Same sums in the same
+// order.  For launches with more workgroups than CUs; up to that the kernel above is as fast or faster.
+template <int K, typename VT>
+__global__ void __launch_bounds__(kAdjThreads, 4) wig_adj_full_kernel(const WigAdjArgs a) {
+    __shared__ WigAdjLds<K, 1, VT, kAdjWaves, true> lds;
+    if ((int)blockIdx.x < a.nplain)
+        wig_adj_body<K, 1, false, VT, kAdjWaves, true>(a, &lds, blockIdx.x, blockIdx.y, threadIdx.x);
+    else wig_adj_body<K, 1, true, VT, kAdjWaves, true>(a, &lds, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
 }  // namespace s2dw
