@@ -1171,6 +1171,15 @@ bool side_by_side(const Plan &P, const Work &w, int maps) {
     return !t_rec && P.s_Ubs > 0 && maps <= side_maps(P) && (size_t)maps * P.s_Ubs <= w.n_Ub;
 }
 
+// The analysis with more than four orders (two passes) in FP64 takes three or fewer scales one by
+// one where their Ub arrays are beyond what stays in the last-level cache from one stage to the
+// next: analysis stages of 64 maps of L = 100, N = 10, three scales (245 MB) 0.794 ms against 0.844
+// together; 24 of L = 128, N = 12 (180 MB) 0.560 against 0.578; with 100 MB or less, or more scales,
+// together is as fast or faster (seven scales of 64 maps of L = 64, N = 10 0.501 against 0.558).
+bool scales_apart(const Plan &P, int f32, int maps) {
+    return !f32 && P.Nh > 4 && P.sns <= 3 && (size_t)maps * P.s_Ubs * sizeof(double2) > (size_t)112 << 20;
+}
+
 hipError_t fused_fwd(const StageArgs &a, const ScaleRefs &refs, int nwg, int P, int maps, bool cx, hipStream_t st) {
     return cx ? launch_fused_fft<true, 2>(a, refs, nwg, P, maps / 2, st)
               : launch_fused_fft<true, 1>(a, refs, nwg, P, maps, st);
@@ -1271,7 +1280,7 @@ int run_inverse(Plan &P, const Shape &sh, Work &w, int maps, const double2 *flm,
     const size_t per_map = P.woff[P.S];  // elements of one W (complex ones with cx)
     const size_t ew = (f32 ? 4 : 8) * (cx ? 2 : 1);
     const int wmaps = cx ? maps / 2 : maps;
-    const bool side = side_by_side(P, w, maps);
+    const bool side = side_by_side(P, w, maps) && !scales_apart(P, f32, maps);
     const size_t s_Ub = side ? P.s_Ubs : P.s_Ub;
     RefList direct, fused;  // scales whose alpha and gamma sums follow the loop
     StageArgs sb{};                       // the arguments all scales share (side by side)
