@@ -1156,6 +1156,19 @@ bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
     return P.nblkb[j] <= 1 || !f32;
 }
 
+// FP64 synthesis of a scale by itself (multiresolution) from about two thousand rings on: two passes
+// where the fused kernel's workgroup has hardly half its threads' samples to sum (transforms of 512
+// with four orders, of 1024 with three or more, of a complex signal four, T not far above a quarter of
+// them).  Whole
+// synthesis, ms, fused against two passes: 100 maps of L = 65, N = 8 0.752, 0.716; of L = 129, N = 6
+// 2.05, 1.96; 16 maps of it 0.407, 0.398; but 16 of L = 65, N = 8 0.191, 0.195; 32 of L = 100, N = 8
+// 0.406, 0.403; 100 of L = 65, N = 6 0.563, 0.582; 32 of L = 257, N = 6 (2048) 2.59, 2.67.
+bool gamma_apart(const Plan &P, int f32, int j, bool cx, bool side, int maps, int nb) {
+    const int size = P.PB[j], T = 2 * P.Lg[j] - 1;
+    return !f32 && !side && P.nblkb[j] <= 1 && (long)maps * nb > 2000 && T <= 3 * size / 10 &&
+           ((size == 512 && P.Nh == 4) || (size == 1024 && P.Nh >= (cx ? 4 : 3)));
+}
+
 // Whether scale j, not taken by fuse_fft, takes the fused alpha and gamma kernel with blocked
 // transforms (fused_blk.hip): against the two passes, round trip L = 700, N = 8, mixed 1.50 ms
 // against 1.58, analysis L = 1024, N = 8 2.01 against 2.05 (FP64).
@@ -1561,7 +1574,8 @@ int run_forward(Plan &P, const Shape &sh, Work &w, int maps, const void *W, cons
         // larger Lj, where the FP32 passes of the mixed path are cheaper
         const bool fused = direct_alpha_gamma(P.Nh, P.ng, Lj, cx) && !f32;
         const bool fused_pfa = !fused && gtab.pcs && !cx && pfa_fused(M, P.Nh) && fuse_adj(P, sh, f32, M);
-        const bool unblk = !fused && fuse_fft(P, f32, j, cx), blk = !fused && !fused_pfa && !unblk && fuse_blk(P, sh, j, cx);
+        const bool unblk = !fused && fuse_fft(P, f32, j, cx) && !gamma_apart(P, f32, j, cx, side, maps, g.L);
+        const bool blk = !fused && !fused_pfa && !unblk && fuse_blk(P, sh, j, cx);
         const bool fused_ch = unblk || blk;
         if (fused_ch) {
             const int nwg = 8 * ((g.L + 7) / 8), size = blk ? P.PBb[j] : P.PB[j];

@@ -26,7 +26,10 @@ def test_default_chunk_fits_its_workspace(L, N, J_min, grid):
 # of L = 230 and 39 of L = 536, N = 1: a batch on either side of the line
 @pytest.mark.parametrize("L,N,J_min,grid,reality,below,beyond", [
     (256, 8, 0, "mw", True, 20, 24), (230, 8, 0, "dh", True, 13, 18), (256, 8, 0, "mw", False, 10, 12),
-    (536, 1, 3, "mw", True, 38, 41)])
+    (536, 1, 3, "mw", True, 38, 41),
+    # batches whose alpha and gamma sums go in two passes (analysis of three scales with five and
+    # more orders; synthesis on grids of their own), a single call's in one launch or one kernel
+    (100, 10, 5, "mw", True, 8, 50), (129, 6, 6, "multires", True, 8, 20), (65, 8, 5, "multires", False, 8, 20)])
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_maps_of_a_batch_equal_single_calls_across_the_line(L, N, J_min, grid, reality, below, beyond, precision):
     print(f"L={L} N={N} {grid} reality={reality} {precision}", flush=True)
