@@ -337,6 +337,17 @@ __device__ __forceinline__ void load_lds16(u32x4 d, unsigned lane_off, unsigned 
                  "s"(__builtin_amdgcn_readfirstlane(off)), "s"(__builtin_amdgcn_readfirstlane(lds))
                  : "m0", "memory");
 }
+// Two loads of one array and one of another, with the wait states of one.
+__device__ __forceinline__ void load_lds16_3(u32x4 da, unsigned lane_a, unsigned off0, unsigned off1, unsigned lds0, unsigned lds1,
+                                             u32x4 db, unsigned lane_b, unsigned offb, unsigned ldsb) {
+    asm volatile("s_mov_b32 m0, %6\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %4 offen lds\n\t"
+                 "s_mov_b32 m0, %7\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %5 offen lds\n\t"
+                 "s_mov_b32 m0, %9\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %8 offen lds" ::"v"(lane_a), "s"(da),
+                 "v"(lane_b), "s"(db), "s"(__builtin_amdgcn_readfirstlane(off0)), "s"(__builtin_amdgcn_readfirstlane(off1)),
+                 "s"(__builtin_amdgcn_readfirstlane(lds0)), "s"(__builtin_amdgcn_readfirstlane(lds1)),
+                 "s"(__builtin_amdgcn_readfirstlane(offb)), "s"(__builtin_amdgcn_readfirstlane(ldsb))
+                 : "m0", "memory");
+}
 template <int N>
 __device__ __forceinline__ void wait_lds() {
     static_assert(N >= 0 && N < 64, "vmcnt");
@@ -576,9 +587,8 @@ __device__ __forceinline__ void wig_fwd_body(const WigFwdArgs &a, WigFwdLds<K, R
     constexpr int kLoads = 5;  // per wave and block
     auto request = [&](int blk, int slot) {
         const unsigned row = (unsigned)blk * 8u + 2u * (unsigned)wave, ro = row * (unsigned)Lp * 8u;
-        load_lds16(fd, fo, 2u * ro, lf + (unsigned)slot * 8192u);
-        load_lds16(fd, fo, 2u * ro + (unsigned)Lp * 16u, lf + (unsigned)slot * 8192u + 1024u);
-        load_lds16(pd, po, ro, lp + (unsigned)slot * 4096u);
+        load_lds16_3(fd, fo, 2u * ro, 2u * ro + (unsigned)Lp * 16u, lf + (unsigned)slot * 8192u,
+                     lf + (unsigned)slot * 8192u + 1024u, pd, po, ro, lp + (unsigned)slot * 4096u);
         if (lane < w.kTabLanes) load_lds16(td, w.to, (unsigned)blk * (128u * K), lt + (unsigned)slot * (R * K * 128u));
         if (lane < w.kULanes) load_lds16(ud, w.uo, (unsigned)blk * 64u, lu + (unsigned)slot * (R * 64u));
     };

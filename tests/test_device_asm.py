@@ -45,20 +45,26 @@ __global__ void probe(const void *src, double *out) {
     assert any(loads[1] < i < loads[2] for i in m0)
 
 
-def test_loads_to_lds_wait_for_scalars_that_a_vector_instruction_wrote(tmp_path):
+@pytest.mark.parametrize("call,loads", [
+    ("load_lds16(desc_of(src), threadIdx.x * 16u, off[threadIdx.x], lds_off(buf))", 1),
+    ("load_lds16_3(desc_of(src), threadIdx.x * 16u, off[threadIdx.x], off[threadIdx.x + 64], lds_off(buf), "
+     "lds_off(buf + 128), desc_of(src), threadIdx.x * 16u, off[threadIdx.x + 128], lds_off(buf + 256))", 3)])
+def test_loads_to_lds_wait_for_scalars_that_a_vector_instruction_wrote(tmp_path, call, loads):
     """Five wait states between a readfirstlane and the load that takes its result as the offset."""
     lines = assembly(tmp_path, """
 __global__ void probe(const void *src, const unsigned *off, double *out) {
-    __shared__ double buf[256];
-    load_lds16(desc_of(src), threadIdx.x * 16u, off[threadIdx.x], lds_off(buf));
+    __shared__ double buf[512];
+    %s;
     wait_lds<0>();
     out[threadIdx.x] = buf[threadIdx.x];
-}""")
-    load = next(i for i, x in enumerate(lines) if x.startswith("buffer_load") and x.endswith("lds"))
-    soffset = lines[load].split(",")[2].split()[0]
-    write = max(i for i, x in enumerate(lines[:load]) if re.match(rf"\S+ {soffset},", x))
-    assert lines[write].startswith("v_readfirstlane_b32")
-    states = 0
-    for x in lines[write + 1:load]:
-        states += int(x.split()[1]) + 1 if x.startswith("s_nop") else 1
-    assert states >= 5
+}""" % call)
+    at = [i for i, x in enumerate(lines) if x.startswith("buffer_load") and x.endswith("lds")]
+    assert len(at) == loads
+    for load in at:
+        soffset = lines[load].split(",")[2].split()[0]
+        write = max(i for i, x in enumerate(lines[:load]) if re.match(rf"\S+ {soffset},", x))
+        assert lines[write].startswith("v_readfirstlane_b32")
+        states = 0
+        for x in lines[write + 1:load]:
+            states += int(x.split()[1]) + 1 if x.startswith("s_nop") else 1
+        assert states >= 5
