@@ -62,14 +62,11 @@ int wig_fwd_slots_for(int K, long waves, int maps) {
 // Mixed precision: one number of slots at every size, so that its FP32 sums over the m' of a group
 // are rounded the same way in every call.
 // FP64: the number follows the size of a map, not of the batch, whose maps have the results of single
-// calls.  The line lies where one slot would make a batch slower by more than it makes a map faster.
-// With one order, two from L = 257 on (8 maps of L = 512, N = 1: 818 us against 1047 with one, one map
-// 125 against 122; 20 maps of L = 256 448 against 529, but one map 109 against 102); with two, from
-// L = 449 on (whole syntheses, N = 4: 24 maps of L = 512 6.25 ms against 7.10 with one, one map 0.374
-// against 0.360; 16 maps of L = 400 2.72 against 2.94, one map 0.300 against 0.283).
+// calls; with one order, two from L = 257 on (8 maps of L = 512, N = 1: 818 us against 1047 with one,
+// one map 125 against 122; 20 maps of L = 256 448 against 529, but one map 109 against 102).
 int wig_adj_slots(int K, long waves, int f32) {
     if (f32) return K >= 5 ? 1 : (K >= 2 ? 2 : 4);
-    return wig_slots(K, waves, K <= 1 ? 1024 : (K == 2 ? 3200 : 5000));
+    return wig_slots(K, waves, K <= 1 ? 1024 : 5000);
 }
 
 // Slot counts compiled for each number of carried orders K (the tile shapes the tuner may pick).
