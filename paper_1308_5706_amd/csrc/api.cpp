@@ -455,7 +455,10 @@ Shape shape_of(Plan &P) {
 // those arrays take no more than this.  Measured, ms, together against scale by scale: round
 // trip L = 640, N = 4 (126 MB) 1.10 against 1.38, 32 maps of L = 128, N = 8, mixed (200 MB) 1.00
 // against 1.15, L = 900, N = 8 (311 MB) 3.55 against 3.82, L = 1500, N = 8 (864 MB) 14.15 against
-// 14.36: beyond it a scale fills the chip by itself and the memory is not worth it.
+// 14.36: beyond it a scale fills the chip by itself and the memory is not worth it.  Nor is a batch
+// beyond it better cut into chunks that fit: 64 maps of L = 256, N = 8 5.42 ms (analysis) and 7.23
+// (synthesis) at once, 5.77 and 7.76 by 21; 20 of L = 512, N = 8 8.11 and 10.45, by 5 8.30 and 10.83; in
+// mixed precision within 3 % either way.
 constexpr size_t kSideBytes = (size_t)512 << 20;
 
 // Maps whose Ub arrays of every scale go side by side: as many as fit kSideBytes (16 bytes an element
@@ -1157,12 +1160,11 @@ bool fuse_fft(const Plan &P, int f32, int j, bool cx) {
 }
 
 // FP64 synthesis of a scale by itself (multiresolution) from about two thousand rings on: two passes
-// where the fused kernel's workgroup has hardly half its threads' samples to sum (transforms of 512
-// with four orders, of 1024 with three or more, of a complex signal four, T not far above a quarter of
-// them).  Whole
-// synthesis, ms, fused against two passes: 100 maps of L = 65, N = 8 0.752, 0.716; of L = 129, N = 6
-// 2.05, 1.96; 16 maps of it 0.407, 0.398; but 16 of L = 65, N = 8 0.191, 0.195; 32 of L = 100, N = 8
-// 0.406, 0.403; 100 of L = 65, N = 6 0.563, 0.582; 32 of L = 257, N = 6 (2048) 2.59, 2.67.
+// where the fused kernel's workgroup has samples for hardly half its threads (transforms of 512 with
+// four orders, of 1024 with three or more, or four of a complex signal, and T not far above a quarter
+// of them).  Whole synthesis, ms, fused against two passes: 100 maps of L = 65, N = 8 0.752, 0.716; of
+// L = 129, N = 6 2.05, 1.96; 16 maps of it 0.407, 0.398; but 16 of L = 65, N = 8 0.191, 0.195; 32 of
+// L = 100, N = 8 0.406, 0.403; 100 of L = 65, N = 6 0.563, 0.582; 32 of L = 257, N = 6 (2048) 2.59, 2.67.
 bool gamma_apart(const Plan &P, int f32, int j, bool cx, bool side, int maps, int nb) {
     const int size = P.PB[j], T = 2 * P.Lg[j] - 1;
     return !f32 && !side && P.nblkb[j] <= 1 && (long)maps * nb > 2000 && T <= 3 * size / 10 &&

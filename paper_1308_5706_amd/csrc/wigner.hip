@@ -45,25 +45,30 @@ static hipError_t launch_adj_k(const WigAdjArgs &a, int ntiles, int maps, hipStr
 // and, in the synthesis, the window sums and the partial sums of a group; but below a few waves
 // per SIMD (1024 of them) a wave's own chain of steps is what takes the time, and fewer slots
 // make it shorter.  Measured (us, one map, FP64; analysis / synthesis with the final sum), slots
-// 1, 2, 4: L = 256, N = 8 (1024 waves at one slot) 43, 61 / 88, 114; L = 421, N = 6 (2947) 59, 77 /
-// 123, 153; L = 512, N = 4 (4096) 87, 76, 122 / 133, 147, 217; L = 512, N = 1 72, 60, 85 / 122, 125,
-// 167; L = 1024, N = 8 (16384) 648, 390 / 804, 582; L = 1024, N = 3 500, 226, 213 / 664, 432, 409;
-// L = 2048, N = 4 3283, 1594, 1454 / 4740, 3131, 2426.
+// 1, 2, 4: L = 256, N = 8 (1024 waves at one slot) 48, 66 / 91, 114; L = 421, N = 6 (2947) 59, 79 /
+// 126, 151; L = 512, N = 4 (4096) 59, 77, 113 / 140, 153, 214; L = 512, N = 1 50, 62, 85 / 128, 126,
+// 169; L = 1024, N = 8 (16384) 456, 395 / 830, 596; L = 1024, N = 3 330, 241, 226 / 561, 466, 414;
+// L = 2048, N = 4 2206, 1713, 1585 / 4199, 3327, 2569.
 static int wig_slots(int K, long waves, long one) {
     const int most = K >= 5 ? 1 : (K >= 3 ? 2 : 4);
     if (waves <= one) return 1;
     return waves <= 12000 && most > 2 ? 2 : most;
 }
-// One order: a batch of small maps takes four slots earlier (28 maps of L = 128: 172 us against 187
-// with two; one map of L = 640 201 with two, 229 with four).
+// One map takes one slot longer than a batch of the same waves, whose chains are shorter (N = 4:
+// L = 576, 5184 waves, 72 us with one slot, 86 with two; L = 640 99 and 96; 16 maps of L = 128, 4096
+// waves, 51 and 45; 4 of L = 256 56 and 63, 6 of them 73 and 70).
+// One order: a batch of small maps takes four slots earlier (24 maps of L = 128: 44 us against 50
+// with two; one map of L = 640 71 with two, 99 with four).
 int wig_fwd_slots_for(int K, long waves, int maps) {
-    return K <= 1 && waves <= 3500 && waves * maps > 6000 ? 4 : wig_slots(K, waves * maps, 3500);
+    return K <= 1 && waves <= 3500 && waves * maps > 6000 ? 4 : wig_slots(K, waves * maps, maps == 1 ? 6000 : 3500);
 }
 // Mixed precision: one number of slots at every size, so that its FP32 sums over the m' of a group
 // are rounded the same way in every call.
 // FP64: the number follows the size of a map, not of the batch, whose maps have the results of single
-// calls; with one order, two from L = 257 on (8 maps of L = 512, N = 1: 818 us against 1047 with one,
-// one map 125 against 122; 20 maps of L = 256 448 against 529, but one map 109 against 102).
+// calls.  One slot is up to 5 % faster for one map and up to 5 % slower for a batch about the line (whole
+// syntheses, ms, one and two slots; N = 1: one map of L = 256 0.090, 0.095, 20 maps 0.473, 0.448; one of
+// L = 512 0.177, 0.175, 8 maps 0.929, 0.820.  N = 4: one of L = 400 0.275, 0.291, 16 maps 2.62, 2.59;
+// one of L = 512 0.347, 0.357, 24 maps 6.43, 6.17; one of L = 600 0.600, 0.612, 8 maps 4.02, 3.93).
 int wig_adj_slots(int K, long waves, int f32) {
     if (f32) return K >= 5 ? 1 : (K >= 2 ? 2 : 4);
     return wig_slots(K, waves, K <= 1 ? 1024 : 5000);
