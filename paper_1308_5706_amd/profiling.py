@@ -36,7 +36,7 @@ STAGE_KERNELS = {  # first match wins: the fused passes before the gamma passes 
     "gamma_alpha_adj": ("gamma_alpha_adj_kernel", "gamma_alpha_adj_pfa_kernel", "gamma_alpha_adj_fft_kernel",
                         "gamma_alpha_adj_blk_kernel"),
     "wigner_fwd": ("wig_fwd_kernel",),
-    "wigner_adj": ("wig_adj_kernel",),
+    "wigner_adj": ("wig_adj_kernel", "wig_adj_full_kernel"),
     "beta_fwd": ("beta_fwd_fft_kernel", "beta_fwd_pair_kernel", "beta_fwd_pfa_kernel"),
     "alpha_fwd": ("alpha_fwd_fft_kernel", "alpha_fwd_blk_kernel", "alpha_fwd_pfa_kernel"),
     "gamma_fwd": ("gamma_fwd_kernel",),
