@@ -16,21 +16,22 @@
 // product to D_{l-1} in place: a product u p and a multiply-add per pair and step.
 //
 // The l-range goes in blocks of eight steps, unrolled; the tables and the per-lane arrays are laid
-// out by block (kernels.h), so that every address advances by a constant.  Most instructions are FP64
-// ones (82-85 %), a multiply-add takes four cycles per SIMD (at two waves per SIMD about five were
-// measured), and everything else is kept out of their way.  They do not fill the SIMDs: the counters
-// show a vector instruction in 56-64 % of the cycles of the analysis and 46-51 % of the synthesis
-// (L = 1024, N = 8 and L = 2048, N = 4); what is left is a wave's own chain of steps, with two waves
-// per SIMD to cover it, the barriers, and in the synthesis the window sums.
+// out by block (kernels.h), so that every address advances by a constant.  About four fifths of the
+// vector instructions are FP64 ones, and a multiply-add takes four cycles per SIMD (at two waves per
+// SIMD about five were measured), so everything else is kept out of their way.  They do not fill the
+// SIMDs: the counters show a vector instruction issued in some 55-65 % of the cycles of the analysis
+// and 45-55 % of the synthesis (L = 1024, N = 8 and L = 2048, N = 4); what is left is a wave's own
+// chain of steps, with two waves per SIMD to cover it, the barriers, and in the synthesis the window
+// sums.
 //  * values that depend on (l, m') only -- ut_l(m') and kappa^j(l) sigma_{l,n} Delta^l_{m'n} h_l(m') -- are
 //    operands of the multiply-adds through a DPP broadcast (below) instead of scalar loads one step
 //    ahead, whose latency the waves waited for;
 //  * the analysis reads g_l(m) f_lm and pt_l(m) from LDS, where loads without registers bring the
 //    workgroup's rows one or more blocks ahead (once per workgroup, not per wave);
 //  * the synthesis sums its window of eight steps over the waves during the next block.
-// Measured against the scalar-load form (us): analysis L = 256, N = 8 121 -> 48; L = 1024, N = 8
-// 602 -> 396; L = 2048, N = 4 2270 -> 1590.  Synthesis with its final sum: 125 -> 91; 738 -> 599;
-// 3360 -> 2580 (there four slots per wave, half the partial sums).
+// Measured against the scalar-load form (us, event pairs around the launch): analysis L = 256, N = 8
+// 121 -> 48; L = 1024, N = 8 602 -> 396; L = 2048, N = 4 2270 -> 1590.  Synthesis with its final sum:
+// 125 -> 91; 738 -> 599; 3360 -> 2580 (there four slots per wave, half the partial sums).
 //
 // Symmetries used (exact identities of Delta): Delta^l_{m',-n} = (-1)^{l+m'}
 // Delta^l_{m'n} lets the l-sum run only over n >= 0 with separate even-l and odd-l
