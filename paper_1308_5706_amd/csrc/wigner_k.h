@@ -336,22 +336,42 @@ __device__ __forceinline__ u32x4 desc_of(const void *p) {
     d.w = 0x00027000u;
     return d;
 }
-__device__ __forceinline__ void load_lds16(u32x4 d, unsigned lane_off, unsigned off, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(lane_off), "s"(d),
-                 "s"(__builtin_amdgcn_readfirstlane(off)), "s"(__builtin_amdgcn_readfirstlane(lds))
-                 : "m0", "memory");
+// One of these loads, after the move to m0 and WAIT + 1 wait states.
+#define S2DW_LDS_LOAD(D, LANE, OFF, LDS, WAIT) \
+    "s_mov_b32 m0, %[" LDS "]\n\ts_nop " WAIT "\n\tbuffer_load_dwordx4 %[" LANE "], %[" D "], %[" OFF "] offen lds\n\t"
+// The lanes below 64 - %[N] only.
+#define S2DW_LDS_LANES(N) "s_lshr_b64 exec, -1, %[" N "]\n\t"
+
+// What a load takes beside the lane offset.
+struct LdsLoad {
+    u32x4 d;
+    unsigned off, lds;
+};
+__device__ __forceinline__ LdsLoad lds_load(u32x4 d, unsigned off, unsigned lds) {
+    return {d, (unsigned)__builtin_amdgcn_readfirstlane(off), (unsigned)__builtin_amdgcn_readfirstlane(lds)};
 }
-// Two loads of one array and one of another, with the wait states of one.
-__device__ __forceinline__ void load_lds16_3(u32x4 da, unsigned lane_a, unsigned off0, unsigned off1, unsigned lds0, unsigned lds1,
-                                             u32x4 db, unsigned lane_b, unsigned offb, unsigned ldsb) {
-    asm volatile("s_mov_b32 m0, %6\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %4 offen lds\n\t"
-                 "s_mov_b32 m0, %7\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %5 offen lds\n\t"
-                 "s_mov_b32 m0, %9\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %8 offen lds" ::"v"(lane_a), "s"(da),
-                 "v"(lane_b), "s"(db), "s"(__builtin_amdgcn_readfirstlane(off0)), "s"(__builtin_amdgcn_readfirstlane(off1)),
-                 "s"(__builtin_amdgcn_readfirstlane(lds0)), "s"(__builtin_amdgcn_readfirstlane(lds1)),
-                 "s"(__builtin_amdgcn_readfirstlane(offb)), "s"(__builtin_amdgcn_readfirstlane(ldsb))
-                 : "m0", "memory");
+// The five loads of a block in one statement, with the wait states of one: a, the same lanes at off_a2
+// to lds_a2, b, and c and d by the first NC and ND lanes.  Every lane is active where it stands.
+template <int NC, int ND>
+__device__ __forceinline__ void load_lds16_5(const LdsLoad &a, unsigned lane_a, unsigned off_a2, unsigned lds_a2,
+                                             const LdsLoad &b, unsigned lane_b, const LdsLoad &c, unsigned lane_c,
+                                             const LdsLoad &d, unsigned lane_d) {
+    static_assert(NC > 0 && NC <= 64 && ND > 0 && ND <= 64, "lanes");
+    unsigned long long exec;
+    asm volatile(S2DW_LDS_LOAD("da", "va", "oa", "la", "3") S2DW_LDS_LOAD("da", "va", "oa2", "la2", "0")
+                     S2DW_LDS_LOAD("db", "vb", "ob", "lb", "0") "s_mov_b64 %[ex], exec\n\t" S2DW_LDS_LANES("nc")
+                         S2DW_LDS_LOAD("dc", "vc", "oc", "lc", "0") S2DW_LDS_LANES("nd")
+                             S2DW_LDS_LOAD("dd", "vd", "od", "ld", "0") "s_mov_b64 exec, %[ex]"
+                 : [ex] "=&s"(exec)
+                 : [da] "s"(a.d), [oa] "s"(a.off), [la] "s"(a.lds), [va] "v"(lane_a),
+                   [oa2] "s"(__builtin_amdgcn_readfirstlane(off_a2)), [la2] "s"(__builtin_amdgcn_readfirstlane(lds_a2)),
+                   [db] "s"(b.d), [ob] "s"(b.off), [lb] "s"(b.lds), [vb] "v"(lane_b), [dc] "s"(c.d), [oc] "s"(c.off),
+                   [lc] "s"(c.lds), [vc] "v"(lane_c), [dd] "s"(d.d), [od] "s"(d.off), [ld] "s"(d.lds), [vd] "v"(lane_d),
+                   [nc] "n"(64 - NC), [nd] "n"(64 - ND)
+                 : "m0", "scc", "memory");
 }
+#undef S2DW_LDS_LANES
+#undef S2DW_LDS_LOAD
 template <int N>
 __device__ __forceinline__ void wait_lds() {
     static_assert(N >= 0 && N < 64, "vmcnt");
@@ -591,10 +611,11 @@ __device__ __forceinline__ void wig_fwd_body(const WigFwdArgs &a, WigFwdLds<K, R
     constexpr int kLoads = 5;  // per wave and block
     auto request = [&](int blk, int slot) {
         const unsigned row = (unsigned)blk * 8u + 2u * (unsigned)wave, ro = row * (unsigned)Lp * 8u;
-        load_lds16_3(fd, fo, 2u * ro, 2u * ro + (unsigned)Lp * 16u, lf + (unsigned)slot * 8192u,
-                     lf + (unsigned)slot * 8192u + 1024u, pd, po, ro, lp + (unsigned)slot * 4096u);
-        if (lane < w.kTabLanes) load_lds16(td, w.to, (unsigned)blk * (128u * K), lt + (unsigned)slot * (R * K * 128u));
-        if (lane < w.kULanes) load_lds16(ud, w.uo, (unsigned)blk * 64u, lu + (unsigned)slot * (R * 64u));
+        load_lds16_5<decltype(w)::kTabLanes, decltype(w)::kULanes>(
+            lds_load(fd, 2u * ro, lf + (unsigned)slot * 8192u), fo, 2u * ro + (unsigned)Lp * 16u,
+            lf + (unsigned)slot * 8192u + 1024u, lds_load(pd, ro, lp + (unsigned)slot * 4096u), po,
+            lds_load(td, (unsigned)blk * (128u * K), lt + (unsigned)slot * (R * K * 128u)), w.to,
+            lds_load(ud, (unsigned)blk * 64u, lu + (unsigned)slot * (R * 64u)), w.uo);
     };
 
     int si = t.z, blk = t.w;
